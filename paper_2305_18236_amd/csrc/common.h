@@ -26,11 +26,11 @@ struct GemmArgs {
     int tiles_m, tiles_n;
     int group_m;      // tile rows per raster group (L2 reuse of B panels)
     int remap;        // 1: give each XCD a contiguous range of tiles (see tile_of)
-    // vec_a / vec_b: 16-byte loads allowed (16-byte aligned, ld % 4 == 0) and
-    // in-panel byte offsets fit 32 bits (ld < 2^22 - 64), which lets interior
-    // panels address through a uniform base plus a 32-bit per-lane offset.
-    // vec_c: 16-byte aligned C with ldc % 4 == 0.
-    int vec_a, vec_b, vec_c;
+    // vec_a / vec_b: in-panel byte offsets fit 32 bits (ld < 2^22 - 64), which
+    // lets panels address through a uniform base plus a 32-bit per-lane
+    // offset, and stored rows hold at least one 4-float chunk.  No alignment
+    // is asked for: 16-byte global accesses need 4-byte alignment only.
+    int vec_a, vec_b;
     // Pre-packed BF16 operands only: element offset from the hi plane of
     // op(A) (op(B)^T) to its lo plane.
     int64_t plane_a, plane_b;
@@ -62,7 +62,6 @@ MG_DEVICE void split_k_view(GemmArgs& g)
     g.ldc = g.ldp;
     g.alpha = 1.f;
     g.beta = 0.f;
-    g.vec_c = 1;
 }
 
 // Arguments of the FP8 GEMM on packed operands (see gemm_fp8.hip).
@@ -103,24 +102,52 @@ MG_DEVICE void tile_of(int pid, int tiles_m, int tiles_n, int group_m, int remap
     tn = local / rows;
 }
 
-// Guarded 16-byte fetch of stored columns gc .. gc+3 of stored row gr of a
-// matrix with R x Cn valid entries (row stride ld); out-of-range elements read
-// 0.  Used only on edge panels: its per-lane branches serialise the loads.
-MG_DEVICE floatx4 fetch4_guarded(const float* __restrict__ src, int64_t ld, int64_t gr, int64_t gc,
-                                 int64_t R, int64_t Cn, bool vec)
+// 16-byte and 8-byte accesses of 4-byte aligned floats.  The global memory
+// path takes them at any 4-byte address: an access that straddles two cache
+// lines costs a second line, not a fault or a scalar sequence.
+typedef floatx4 floatx4u __attribute__((aligned(4)));
+typedef floatx2 floatx2u __attribute__((aligned(4)));
+
+// The valid part of a block of a stored matrix whose first element is (r0, c0)
+// of R x Cn valid entries: rows and columns from the block's first (not above
+// zero where the block lies outside), and whether the matrix has a whole
+// W-element chunk.
+struct Valid {
+    int rows, cols;
+    bool wide;
+};
+
+MG_DEVICE Valid valid_part(int64_t r0, int64_t c0, int64_t R, int64_t Cn, int W)
 {
-    floatx4 x = {0.f, 0.f, 0.f, 0.f};
-    if (gr < R) {
-        const float* p = src + gr * ld + gc;
-        if (vec && gc + 3 < Cn) {
-            x = *reinterpret_cast<const floatx4*>(p);
-        } else {
-            if (gc + 0 < Cn) x[0] = p[0];
-            if (gc + 1 < Cn) x[1] = p[1];
-            if (gc + 2 < Cn) x[2] = p[2];
-            if (gc + 3 < Cn) x[3] = p[3];
-        }
-    }
+    const int64_t big = 1 << 20;
+    return {int(min(R - r0, big)), int(min(Cn - c0, big)), Cn >= W};
+}
+
+// Fetch of columns c .. c+3 of row r of a block where any of them may lie
+// outside the matrix (src: the block's first element): those read 0.  Two
+// halves without per-lane branches, so that a caller can put the loads of all
+// its chunks in flight before the first is looked at: edge_load reads the
+// chunk moved left and up until it is inside, edge_fix moves the values back
+// and clears the rest.
+MG_DEVICE floatx4 edge_load(const float* __restrict__ src, int64_t ld, int r, int c, Valid b)
+{
+    const float* __restrict__ p = src + min(r, b.rows - 1) * ld;
+    if (b.wide) return *reinterpret_cast<const floatx4u*>(p + min(c, b.cols - 4));   // uniform
+    return floatx4{p[min(c, b.cols - 1)], p[min(c + 1, b.cols - 1)], p[min(c + 2, b.cols - 1)],
+                   p[min(c + 3, b.cols - 1)]};
+}
+
+MG_DEVICE floatx4 edge_fix(floatx4 w, int r, int c, Valid b)
+{
+    const int left = max(0, min(4, b.cols - c));   // valid columns of the chunk
+    const int keep = r < b.rows ? left : 0;
+    const int sh = b.wide ? 4 - left : 0;          // how far the chunk was moved left
+    floatx4 x = w;
+    if (sh & 1) x = floatx4{x[1], x[2], x[3], 0.f};
+    if (sh & 2) x = floatx4{x[2], x[3], 0.f, 0.f};
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+        if (e >= keep) x[e] = 0.f;
     return x;
 }
 
@@ -128,7 +155,7 @@ MG_DEVICE floatx4 fetch4_guarded(const float* __restrict__ src, int64_t ld, int6
 // form the global_load ... saddr instructions take (one VGPR per address).
 MG_DEVICE floatx4 load16(const float* __restrict__ base, uint32_t byte_off)
 {
-    return *reinterpret_cast<const floatx4*>(reinterpret_cast<const char*>(base) + byte_off);
+    return *reinterpret_cast<const floatx4u*>(reinterpret_cast<const char*>(base) + byte_off);
 }
 
 MG_DEVICE uint4 load16u(const void* __restrict__ base, uint32_t byte_off)

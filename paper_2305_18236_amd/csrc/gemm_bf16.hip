@@ -316,8 +316,18 @@ __global__ __launch_bounds__(256) void bf16_pack_kernel(const float* __restrict_
 #pragma unroll
         for (int s = 0; s < 16; ++s) v[s] = load16(base, (uint32_t(stored_row(s)) * ld32 + uint32_t(stored_col(s))) * 4u);
     } else {
+        const Valid part = valid_part(sr0, sc0, SRn, SCn, 4);
 #pragma unroll
-        for (int s = 0; s < 16; ++s) v[s] = fetch4_guarded(X, ldx, sr0 + stored_row(s), sc0 + stored_col(s), SRn, SCn, vec);
+        for (int s = 0; s < 16; ++s) {
+            v[s] = floatx4{0.f, 0.f, 0.f, 0.f};
+            if (stored_row(s) < part.rows && stored_col(s) < part.cols)
+                v[s] = edge_load(X + sr0 * ldx + sc0, ldx, stored_row(s), stored_col(s), part);
+        }
+        // a chunk straddles the last column (wave-uniform)
+        if (part.cols < PT && (part.cols & 3) != 0) {
+#pragma unroll
+            for (int s = 0; s < 16; ++s) v[s] = edge_fix(v[s], stored_row(s), stored_col(s), part);
+        }
     }
     auto convert = [&](floatx4 x, uint32_t (&h)[2], uint32_t (&l)[2]) {
         if constexpr (TERMS == 3) split4(x, h, l);

@@ -122,8 +122,7 @@ __global__ __launch_bounds__(256) void scale_c_kernel(float* C, int64_t M, int64
 // handles four consecutive columns of one row per step.
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restrict__ part, int64_t ldp,
                                                             int64_t stride, int S, float* C, int64_t ldc,
-                                                            int64_t M, int64_t N, float alpha, float beta,
-                                                            int vec_c)
+                                                            int64_t M, int64_t N, float alpha, float beta)
 {
     const int64_t n4 = (N + 3) / 4;
     const int64_t total = M * n4;
@@ -137,16 +136,16 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restr
             acc[0] += x[0]; acc[1] += x[1]; acc[2] += x[2]; acc[3] += x[3];
         }
         float* c = C + i * ldc + j;
-        if (vec_c && j + 3 < N) {
+        if (j + 3 < N) {
             floatx4 o = {alpha * acc[0], alpha * acc[1], alpha * acc[2], alpha * acc[3]};
             if (beta != 0.f) {
-                const floatx4 c0 = *reinterpret_cast<const floatx4*>(c);
+                const floatx4 c0 = *reinterpret_cast<const floatx4u*>(c);
                 o[0] = __builtin_fmaf(alpha, acc[0], beta * c0[0]);
                 o[1] = __builtin_fmaf(alpha, acc[1], beta * c0[1]);
                 o[2] = __builtin_fmaf(alpha, acc[2], beta * c0[2]);
                 o[3] = __builtin_fmaf(alpha, acc[3], beta * c0[3]);
             }
-            *reinterpret_cast<floatx4*>(c) = o;
+            *reinterpret_cast<floatx4u*>(c) = o;
         } else {
             for (int e = 0; e < 4 && j + e < N; ++e) {
                 float o = alpha * acc[e];
@@ -162,9 +161,8 @@ hipError_t launch_splitk_reduce(const GemmArgs& g, int splits, float* C, int64_t
     const int64_t total = g.M * ((g.N + 3) / 4);
     int64_t blocks = (total + 255) / 256;
     if (blocks > 8192) blocks = 8192;
-    const int vec_c = (reinterpret_cast<uintptr_t>(C) & 15) == 0 && ldc % 4 == 0;
     hipLaunchKernelGGL(splitk_reduce_kernel, dim3(unsigned(blocks)), dim3(256), 0, stream, g.part, g.ldp,
-                       g.part_stride, splits, C, ldc, g.M, g.N, g.alpha, g.beta, vec_c);
+                       g.part_stride, splits, C, ldc, g.M, g.N, g.alpha, g.beta);
     return hipGetLastError();
 }
 

@@ -70,7 +70,7 @@ MG_DEVICE int qt_swizzle(int r, int k) { return 16 * (((k >> 4) ^ ((r >> 2) + (r
 // op(X).  T == false: X stored R x Kd (k contiguous); T == true: stored Kd x R.
 template <bool T>
 __global__ __launch_bounds__(256) void fp8_pack_kernel(const float* __restrict__ X, int64_t ldx,
-                                                       int64_t R, int64_t Kd, int vec,
+                                                       int64_t R, int64_t Kd,
                                                        uint8_t* __restrict__ q, int64_t ldq,
                                                        uint8_t* __restrict__ sc, int64_t lds)
 {
@@ -97,13 +97,26 @@ __global__ __launch_bounds__(256) void fp8_pack_kernel(const float* __restrict__
     // stored tile origin and valid extent
     const int64_t sr0 = T ? k0 : r0, sc0 = T ? r0 : k0;
     const int64_t SRn = T ? Kd : R, SCn = T ? R : Kd;
-    if (vec && sr0 + QT <= SRn && sc0 + QT <= SCn) {   // wave-uniform: interior tile
+    if (sr0 + QT <= SRn && sc0 + QT <= SCn) {   // wave-uniform: interior tile
         const float* __restrict__ base = X + sr0 * ldx + sc0;
 #pragma unroll
-        for (int s = 0; s < 16; ++s) v[s] = *reinterpret_cast<const floatx4*>(base + stored_row(s) * ldx + stored_col(s));
-    } else {
+        for (int s = 0; s < 16; ++s) v[s] = *reinterpret_cast<const floatx4u*>(base + stored_row(s) * ldx + stored_col(s));
+    } else if (R == 0 || Kd == 0) {
 #pragma unroll
-        for (int s = 0; s < 16; ++s) v[s] = fetch4_guarded(X, ldx, sr0 + stored_row(s), sc0 + stored_col(s), SRn, SCn, vec);
+        for (int s = 0; s < 16; ++s) v[s] = floatx4{0.f, 0.f, 0.f, 0.f};
+    } else {
+        const Valid part = valid_part(sr0, sc0, SRn, SCn, 4);
+#pragma unroll
+        for (int s = 0; s < 16; ++s) {
+            v[s] = floatx4{0.f, 0.f, 0.f, 0.f};
+            if (stored_row(s) < part.rows && stored_col(s) < part.cols)
+                v[s] = edge_load(X + sr0 * ldx + sc0, ldx, stored_row(s), stored_col(s), part);
+        }
+        // a chunk straddles the last column (wave-uniform)
+        if (part.cols < QT && (part.cols & 3) != 0) {
+#pragma unroll
+            for (int s = 0; s < 16; ++s) v[s] = edge_fix(v[s], stored_row(s), stored_col(s), part);
+        }
     }
     float amax = 0.f;
 #pragma unroll
@@ -151,13 +164,13 @@ __global__ __launch_bounds__(256) void fp8_pack_kernel(const float* __restrict__
     if (tid == 0) sc[rt * lds + kt] = uint8_t(sbyte);
 }
 
-hipError_t launch_fp8_pack(bool trans, const float* X, int64_t ldx, int64_t R, int64_t Kd, bool vec,
-                           uint8_t* q, int64_t ldq, uint8_t* sc, int64_t lds, int64_t Rp, int64_t Kp,
+hipError_t launch_fp8_pack(bool trans, const float* X, int64_t ldx, int64_t R, int64_t Kd, uint8_t* q,
+                           int64_t ldq, uint8_t* sc, int64_t lds, int64_t Rp, int64_t Kp,
                            hipStream_t stream)
 {
     const dim3 grid(unsigned(trans ? Rp / QT : Kp / QT), unsigned(trans ? Kp / QT : Rp / QT)), block(256);
-    if (trans) hipLaunchKernelGGL(fp8_pack_kernel<true>, grid, block, 0, stream, X, ldx, R, Kd, int(vec), q, ldq, sc, lds);
-    else hipLaunchKernelGGL(fp8_pack_kernel<false>, grid, block, 0, stream, X, ldx, R, Kd, int(vec), q, ldq, sc, lds);
+    if (trans) hipLaunchKernelGGL(fp8_pack_kernel<true>, grid, block, 0, stream, X, ldx, R, Kd, q, ldq, sc, lds);
+    else hipLaunchKernelGGL(fp8_pack_kernel<false>, grid, block, 0, stream, X, ldx, R, Kd, q, ldq, sc, lds);
     return hipGetLastError();
 }
 

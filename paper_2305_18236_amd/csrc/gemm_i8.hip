@@ -43,10 +43,11 @@ MG_DEVICE int it_swizzle(int r, int k) { return 16 * (((k >> 4) ^ (r >> 4)) & 7)
 
 // One workgroup of 256 threads per 128 x 128 tile of the logical R x Kd
 // matrix op(X).  T == false: X stored R x Kd (k contiguous); T == true:
-// stored Kd x R.  vec: 16-byte aligned X with ldx % 16 == 0.
+// stored Kd x R.  16-byte loads at any address (an odd row stride or base
+// costs the lines that a load straddles).
 template <bool T>
 __global__ __launch_bounds__(256) void i8_pack_kernel(const int8_t* __restrict__ X, int64_t ldx, int64_t R,
-                                                      int64_t Kd, int vec, int8_t* __restrict__ q, int64_t ldq)
+                                                      int64_t Kd, int8_t* __restrict__ q, int64_t ldq)
 {
     constexpr int ROW = T ? IT : IROW;
     __shared__ __attribute__((aligned(16))) uint8_t tile[IT * ROW];
@@ -67,36 +68,28 @@ __global__ __launch_bounds__(256) void i8_pack_kernel(const int8_t* __restrict__
     // one 4-byte word.  Either way 8 lanes read one 128-byte stored row.
     auto stored_row = [&](int s) { return T ? 4 * (tid / 8) + s : (tid + 256 * s) / 8; };
     auto stored_col = [&](int s) { return T ? 16 * (tid % 8) : 16 * ((tid + 256 * s) % 8); };
-    uint4 v[4];
-    if (vec && sr0 + IT <= SRn && sc0 + IT <= SCn) {          // wave-uniform: interior tile
+    uintx4 w[4];
+    if (sr0 + IT <= SRn && sc0 + IT <= SCn) {                 // wave-uniform: interior tile
         const int8_t* __restrict__ base = X + sr0 * ldx + sc0;
-        const uint32_t ld32 = uint32_t(ldx);
 #pragma unroll
-        for (int s = 0; s < 4; ++s) v[s] = load16u(base, uint32_t(stored_row(s)) * ld32 + uint32_t(stored_col(s)));
+        for (int s = 0; s < 4; ++s) w[s] = *reinterpret_cast<const uintx4u*>(base + stored_row(s) * ldx + stored_col(s));
+    } else if (R == 0 || Kd == 0) {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) w[s] = uintx4{0, 0, 0, 0};
     } else {
+        const Valid part = valid_part(sr0, sc0, SRn, SCn, 16);
+        const uint8_t* __restrict__ src = reinterpret_cast<const uint8_t*>(X) + sr0 * ldx + sc0;
 #pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            const int64_t gr = sr0 + stored_row(s), gc = sc0 + stored_col(s);
-            uint8_t b[16];
+        for (int s = 0; s < 4; ++s) w[s] = edge_load_bytes(src, ldx, stored_row(s), stored_col(s), part);
 #pragma unroll
-            for (int e = 0; e < 16; ++e)
-                b[e] = (gr < SRn && gc + e < SCn) ? uint8_t(X[gr * ldx + gc + e]) : uint8_t(0);
-            uint32_t w[4];
-#pragma unroll
-            for (int d = 0; d < 4; ++d)
-                w[d] = uint32_t(b[4 * d]) | (uint32_t(b[4 * d + 1]) << 8) | (uint32_t(b[4 * d + 2]) << 16) |
-                       (uint32_t(b[4 * d + 3]) << 24);
-            v[s] = make_uint4(w[0], w[1], w[2], w[3]);
-        }
+        for (int s = 0; s < 4; ++s) w[s] = edge_fix_bytes(w[s], stored_row(s), stored_col(s), part);
     }
     if (!T) {
 #pragma unroll
         for (int s = 0; s < 4; ++s)   // stored row = logical row, columns = k .. k+15
-            *reinterpret_cast<uint4*>(&tile[stored_row(s) * IROW + stored_col(s)]) = v[s];
+            *reinterpret_cast<uintx4*>(&tile[stored_row(s) * IROW + stored_col(s)]) = w[s];
     } else {
         const int kk = 4 * (tid / 8);                  // first k of the block
-        const uint32_t w[4][4] = {{v[0].x, v[0].y, v[0].z, v[0].w}, {v[1].x, v[1].y, v[1].z, v[1].w},
-                                  {v[2].x, v[2].y, v[2].z, v[2].w}, {v[3].x, v[3].y, v[3].z, v[3].w}};
 #pragma unroll
         for (int c = 0; c < 16; ++c) {
             const int r = 16 * (tid % 8) + c;          // logical row
@@ -116,12 +109,12 @@ __global__ __launch_bounds__(256) void i8_pack_kernel(const int8_t* __restrict__
     }
 }
 
-hipError_t launch_i8_pack(bool trans, const int8_t* X, int64_t ldx, int64_t R, int64_t Kd, bool vec, int8_t* q,
-                          int64_t ldq, int64_t Rp, int64_t Kp, hipStream_t stream)
+hipError_t launch_i8_pack(bool trans, const int8_t* X, int64_t ldx, int64_t R, int64_t Kd, int8_t* q, int64_t ldq,
+                          int64_t Rp, int64_t Kp, hipStream_t stream)
 {
     const dim3 grid(unsigned(trans ? Rp / IT : Kp / IT), unsigned(trans ? Kp / IT : Rp / IT)), block(256);
-    if (trans) hipLaunchKernelGGL(i8_pack_kernel<true>, grid, block, 0, stream, X, ldx, R, Kd, int(vec), q, ldq);
-    else hipLaunchKernelGGL(i8_pack_kernel<false>, grid, block, 0, stream, X, ldx, R, Kd, int(vec), q, ldq);
+    if (trans) hipLaunchKernelGGL(i8_pack_kernel<true>, grid, block, 0, stream, X, ldx, R, Kd, q, ldq);
+    else hipLaunchKernelGGL(i8_pack_kernel<false>, grid, block, 0, stream, X, ldx, R, Kd, q, ldq);
     return hipGetLastError();
 }
 

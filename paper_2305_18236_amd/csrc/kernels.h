@@ -40,8 +40,8 @@ hipError_t launch_bf16_split(const float* x, int64_t n, uint16_t* hi, uint16_t* 
 extern const SgemmConfig kFp8Configs[];
 extern const int kNumFp8Configs;
 
-hipError_t launch_fp8_pack(bool trans, const float* X, int64_t ldx, int64_t R, int64_t Kd, bool vec,
-                           uint8_t* q, int64_t ldq, uint8_t* sc, int64_t lds, int64_t Rp, int64_t Kp,
+hipError_t launch_fp8_pack(bool trans, const float* X, int64_t ldx, int64_t R, int64_t Kd, uint8_t* q,
+                           int64_t ldq, uint8_t* sc, int64_t lds, int64_t Rp, int64_t Kp,
                            hipStream_t stream);
 hipError_t launch_gemm_fp8(int cfg, Fp8Args g, hipStream_t stream);
 
@@ -97,8 +97,8 @@ struct I8Args {
 };
 extern const SgemmConfig kI8Configs[];
 extern const int kNumI8Configs;
-hipError_t launch_i8_pack(bool trans, const int8_t* X, int64_t ldx, int64_t R, int64_t Kd, bool vec, int8_t* q,
-                          int64_t ldq, int64_t Rp, int64_t Kp, hipStream_t stream);
+hipError_t launch_i8_pack(bool trans, const int8_t* X, int64_t ldx, int64_t R, int64_t Kd, int8_t* q, int64_t ldq,
+                          int64_t Rp, int64_t Kp, hipStream_t stream);
 hipError_t launch_gemm_i8(int cfg, I8Args g, hipStream_t stream);
 hipError_t launch_scale_c_i32(int32_t* C, int64_t M, int64_t N, int64_t ldc, int32_t beta, hipStream_t stream);
 

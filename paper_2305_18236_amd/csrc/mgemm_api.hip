@@ -81,10 +81,9 @@ int validate(char transA, char transB, int64_t M, int64_t N, int64_t K, const vo
     return MG_OK;
 }
 
-bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
-
-// 16-byte panel loads with 32-bit in-panel offsets (see GemmArgs::vec_a).
-bool fast_operand(const void* p, int64_t ld) { return aligned16(p) && ld % 4 == 0 && ld < (int64_t(1) << 22) - 64; }
+// 16-byte panel loads with 32-bit in-panel offsets (see GemmArgs::vec_a) of a
+// stored matrix with rows of `cols` elements, ld apart.
+bool fast_operand(int64_t cols, int64_t ld) { return cols >= 4 && ld < (int64_t(1) << 22) - 64; }
 
 // A dimension no compute entry point accepts (they return MG_ERR_TOO_LARGE);
 // the query functions answer for it without forming products that overflow.
@@ -711,8 +710,7 @@ I8Workspace i8_workspace(int64_t M, int64_t N, int64_t K)
 
 int run_i8_pack(bool trans, int64_t R, int64_t K, const int8_t* X, int64_t ldx, int8_t* q, hipStream_t stream)
 {
-    const bool vec = aligned16(X) && ldx % 16 == 0;
-    return hip_status(mg::launch_i8_pack(trans, X, ldx, R, K, vec, q, fp8_kp(K), fp8_rows(R), fp8_kp(K), stream));
+    return hip_status(mg::launch_i8_pack(trans, X, ldx, R, K, q, fp8_kp(K), fp8_rows(R), fp8_kp(K), stream));
 }
 
 int run_i8_packed(int64_t M, int64_t N, int64_t K, int32_t alpha, const int8_t* qA, const int8_t* qB, int32_t beta,
@@ -750,8 +748,7 @@ int run_fp8_pack(bool trans, int64_t R, int64_t K, const float* X, int64_t ldx, 
                  uint8_t* sc, hipStream_t stream)
 {
     const int64_t Rp = fp8_rows(R), Kp = fp8_kp(K);
-    const bool vec = aligned16(X) && ldx % 4 == 0;
-    return hip_status(mg::launch_fp8_pack(trans, X, ldx, R, K, vec, q, Kp, sc, Kp / 128, Rp, Kp, stream));
+    return hip_status(mg::launch_fp8_pack(trans, X, ldx, R, K, q, Kp, sc, Kp / 128, Rp, Kp, stream));
 }
 
 // forced > tuned for this exact shape > tuned for its bucket > default
@@ -818,9 +815,9 @@ int run_gemm(int path, bool ta, bool tb, int64_t M, int64_t N, int64_t K, float 
     const TileOrder o = tile_order(path);
     g.group_m = o.group_m;
     g.remap = o.remap;
-    g.vec_a = fast_operand(A, lda);
-    g.vec_b = fast_operand(B, ldb);
-    g.vec_c = aligned16(C) && ldc % 4 == 0;
+    const bool va = fast_operand(ta ? M : K, lda), vb = fast_operand(tb ? K : N, ldb);
+    g.vec_a = va;
+    g.vec_b = vb;
     const bool split = split_ws != nullptr && plan.splits > 1;
     if (split) {
         g.part = static_cast<float*>(split_ws);
@@ -849,10 +846,10 @@ int run_gemm(int path, bool ta, bool tb, int64_t M, int64_t N, int64_t K, float 
         if (terms == 3) {
             // interleaved planes (configuration 6): A at a_hi, B at b_hi,
             // 2 Kp elements per row, both terms in one plane
-            hipError_t e = mg::launch_bf16_pack_interleaved(ta, A, lda, M, K, fast_operand(A, lda), ahi, 2 * w.Kp,
+            hipError_t e = mg::launch_bf16_pack_interleaved(ta, A, lda, M, K, va, ahi, 2 * w.Kp,
                                                             w.Mp, w.Kp, stream);
             if (e != hipSuccess) return hip_status(e);
-            e = mg::launch_bf16_pack_interleaved(!tb, B, ldb, N, K, fast_operand(B, ldb), bhi, 2 * w.Kp, w.Np, w.Kp,
+            e = mg::launch_bf16_pack_interleaved(!tb, B, ldb, N, K, vb, bhi, 2 * w.Kp, w.Np, w.Kp,
                                                  stream);
             if (e != hipSuccess) return hip_status(e);
             g.A = reinterpret_cast<const float*>(ahi);
@@ -860,11 +857,11 @@ int run_gemm(int path, bool ta, bool tb, int64_t M, int64_t N, int64_t K, float 
             g.lda = g.ldb = 2 * w.Kp;
             return finish(mg::launch_gemm_bf16(terms, cfg, false, true, g, stream, true));
         }
-        hipError_t e = mg::launch_bf16_pack(ta, terms, A, lda, M, K, fast_operand(A, lda), ahi, alo, w.Kp,
+        hipError_t e = mg::launch_bf16_pack(ta, terms, A, lda, M, K, va, ahi, alo, w.Kp,
                                             w.Mp, w.Kp, stream);
         if (e != hipSuccess) return hip_status(e);
         // op(B)^T is N x K: stored as is when transB is 'T', transposed when 'N'
-        e = mg::launch_bf16_pack(!tb, terms, B, ldb, N, K, fast_operand(B, ldb), bhi, blo, w.Kp, w.Np, w.Kp,
+        e = mg::launch_bf16_pack(!tb, terms, B, ldb, N, K, vb, bhi, blo, w.Kp, w.Np, w.Kp,
                                  stream);
         if (e != hipSuccess) return hip_status(e);
         g.A = reinterpret_cast<const float*>(ahi);
@@ -1217,9 +1214,8 @@ int mg_syr2k(int path, char uplo, char trans, int64_t N, int64_t K, float alpha,
     g.M = N; g.N = N; g.K = K;
     g.lda = lda; g.ldb = ldb; g.ldc = ldc;
     g.alpha = alpha; g.beta = beta;
-    g.vec_a = fast_operand(A, lda);
-    g.vec_b = fast_operand(B, ldb);
-    g.vec_c = aligned16(C) && ldc % 4 == 0;
+    g.vec_a = fast_operand(cols, lda);
+    g.vec_b = fast_operand(cols, ldb);
     const bool split = plan.splits > 1 && workspace != nullptr && workspace_bytes >= plan.bytes &&
                        (reinterpret_cast<uintptr_t>(workspace) & 255) == 0;
     if (!split) return hip_status(mg::launch_syr2k(plan.cfg, lower, tr, 1, g, s));
@@ -1534,9 +1530,8 @@ int run_batched(int path, int64_t count, const mg_problem* problems, void* works
         b.g.tiles_m = int((q.M + c.bm - 1) / c.bm);
         b.g.tiles_n = int((q.N + c.bn - 1) / c.bn);
         b.g.group_m = 1;
-        b.g.vec_a = fast_operand(q.A, q.lda);
-        b.g.vec_b = fast_operand(q.B, q.ldb);
-        b.g.vec_c = aligned16(q.C) && q.ldc % 4 == 0;
+        b.g.vec_a = fast_operand(b.ta ? q.M : q.K, q.lda);
+        b.g.vec_b = fast_operand(b.tb ? q.K : q.N, q.ldb);
         host.push_back(b);
     }
     if (host.empty()) return MG_OK;

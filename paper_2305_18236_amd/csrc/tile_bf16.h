@@ -123,59 +123,58 @@ struct BfPanel {
     static constexpr int LOADS = KSRC ? PER : 4 * PER;
     floatx4 v[LOADS];
 
-    // mn0: first row (m or n) of the panel; k0: first k.  R x Cn: valid extent
-    // of the stored matrix.
-    MG_DEVICE void load(const float* __restrict__ src, int64_t ld, int64_t mn0, int64_t k0,
-                        int64_t R, int64_t Cn, bool vec, int tid)
+    // Byte offsets of a thread's chunks (blocks: of their first k row) from
+    // the panel's first element, clamped where the panel overhangs in m or n
+    // (see PanelLoader in tile_f32.h, the same scheme); blocks past the panel
+    // are not loaded.
+    struct Offsets {
+        uint32_t at[PER];
+    };
+
+    MG_DEVICE static Offsets offsets(int64_t ld, int64_t mn0, int64_t MN, int tid)
     {
-        // stored-panel origin and extent: KSRC rows are mn, columns k; else rows k, columns mn
-        const int64_t r0 = KSRC ? mn0 : k0, c0 = KSRC ? k0 : mn0;
-        const int SR = KSRC ? ROWS : BK, SC = KSRC ? BK : ROWS;
-        // Wave-uniform test: interior panels take the branch-free path, so all
-        // their loads are in flight at once; edge panels take the guarded path.
-        if (vec && r0 + SR <= R && c0 + SC <= Cn) {
-            // uniform base + 32-bit per-lane offset (vec guarantees it fits)
-            const float* __restrict__ base = src + r0 * ld + c0;
-            const uint32_t ld32 = uint32_t(ld);
-            if (KSRC) {
+        const uint32_t ld32 = uint32_t(ld);
+        const uint32_t last = KSRC ? uint32_t(min(int64_t(ROWS - 1), MN - 1 - mn0))
+                                   : uint32_t(min(int64_t(ROWS - 4), (MN - 1 - mn0) & ~int64_t(3)));
+        Offsets o;
 #pragma unroll
-                for (int s = 0; s < PER; ++s) {
-                    const int q = tid + s * NT;
-                    if (CHUNKS % NT != 0 && q >= CHUNKS) break;
-                    const uint32_t r = row_perm(q / (BK / 4)), c = (q % (BK / 4)) * 4;
-                    v[s] = load16(base, (r * ld32 + c) * 4u);
-                }
-            } else {
+        for (int s = 0; s < PER; ++s) {
+            const uint32_t q = tid + s * NT;
+            o.at[s] = KSRC ? (min(uint32_t(row_perm(q / (BK / 4))), last) * ld32 + (q % (BK / 4)) * 4) * 4u
+                           : (4 * (q % (BK / 4)) * ld32 + min(4 * (q / (BK / 4)), last)) * 4u;
+        }
+        return o;
+    }
+
+    // mn0: first row (m or n) of the panel; k0: first k; MN, K: valid extents.
+    MG_DEVICE void load(const float* __restrict__ src, int64_t ld, int64_t mn0, int64_t k0, int64_t MN, int64_t K,
+                        bool vec, const Offsets& o, int tid)
+    {
+        const int64_t need = !KSRC && mn0 + ROWS > MN && (MN & 3) != 0 ? BK + 1 : BK;
+        if (vec && k0 + need <= K) {   // wave-uniform
+            const float* __restrict__ base = KSRC ? src + mn0 * ld + k0 : src + k0 * ld + mn0;
 #pragma unroll
-                for (int b = 0; b < PER; ++b) {
-                    const int q = tid + b * NT;
-                    if (BLOCKS % NT != 0 && q >= BLOCKS) break;
-                    const uint32_t kb = q % (BK / 4), mb = q / (BK / 4);
+            for (int s = 0; s < PER; ++s) {
+                if ((KSRC ? CHUNKS : BLOCKS) % NT != 0 && tid + s * NT >= (KSRC ? CHUNKS : BLOCKS)) break;
+                if (KSRC) {
+                    v[s] = load16(base, o.at[s]);
+                } else {
 #pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        v[4 * b + e] = load16(base, ((4 * kb + e) * ld32 + 4 * mb) * 4u);
+                    for (int e = 0; e < 4; ++e) v[4 * s + e] = load16(base + e * ld, o.at[s]);
                 }
             }
         } else {
-            if (KSRC) {
+            // (opaque: its addresses are not kept in registers over the K loop)
+            int t = tid;
+            asm volatile("" : "+v"(t));
+            auto row = [&](int s) { return KSRC ? row_perm((t + s * NT) / (BK / 4)) : 4 * ((t + (s >> 2) * NT) % (BK / 4)) + (s & 3); };
+            auto col = [&](int s) { return KSRC ? ((t + s * NT) % (BK / 4)) * 4 : 4 * ((t + (s >> 2) * NT) / (BK / 4)); };
+            const Valid b = KSRC ? valid_part(mn0, k0, MN, K, 4) : valid_part(k0, mn0, K, MN, 4);
+            const float* __restrict__ base = KSRC ? src + mn0 * ld + k0 : src + k0 * ld + mn0;
 #pragma unroll
-                for (int s = 0; s < PER; ++s) {
-                    const int q = tid + s * NT;
-                    if (CHUNKS % NT != 0 && q >= CHUNKS) break;
-                    const int r = row_perm(q / (BK / 4)), c = (q % (BK / 4)) * 4;
-                    v[s] = fetch4_guarded(src, ld, mn0 + r, k0 + c, R, Cn, vec);
-                }
-            } else {
+            for (int s = 0; s < LOADS; ++s) v[s] = edge_load(base, ld, row(s), col(s), b);
 #pragma unroll
-                for (int b = 0; b < PER; ++b) {
-                    const int q = tid + b * NT;
-                    if (BLOCKS % NT != 0 && q >= BLOCKS) break;
-                    const int kb = q % (BK / 4), mb = q / (BK / 4);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        v[4 * b + e] = fetch4_guarded(src, ld, k0 + 4 * kb + e, mn0 + 4 * mb, R, Cn, vec);
-                }
-            }
+            for (int s = 0; s < LOADS; ++s) v[s] = edge_fix(v[s], row(s), col(s), b);
         }
     }
 
@@ -238,6 +237,9 @@ struct BfPackedPanel {
     static constexpr int NL = (TERMS == 3) ? 2 : 1;
     static_assert(ROWS % 16 == 0, "row permutation works on groups of 16 rows");
     uint4 v[NL][PER];
+
+    struct Offsets {};
+    MG_DEVICE static Offsets offsets(int64_t, int64_t, int64_t, int) { return {}; }
 
     MG_DEVICE void load(const uint16_t* __restrict__ hi, int64_t plane, int64_t ld, int64_t mn0,
                         int64_t k0, int tid)
@@ -308,18 +310,17 @@ MG_DEVICE void bf16_tile(const GemmArgs& g, int tm, int tn, uint16_t* smem)
 
     typename BfLoaderSel<PACKED, BM, BK, LDR, NT, !TA, TERMS>::type pa;
     typename BfLoaderSel<PACKED, BN, BK, LDR, NT, TB, TERMS>::type pb;
-    // Stored extents: A is M x K ('N') or K x M ('T'); B is K x N ('N') or N x K ('T').
-    const int64_t Ra = TA ? g.K : g.M, Ca = TA ? g.M : g.K;
-    const int64_t Rb = TB ? g.N : g.K, Cb = TB ? g.K : g.N;
-    (void)Ra; (void)Ca; (void)Rb; (void)Cb;
+    // A is stored M x K ('N') or K x M ('T'); B is stored K x N ('N') or N x K ('T').
+    const auto oa = decltype(pa)::offsets(g.lda, m0, g.M, tid);
+    const auto ob = decltype(pb)::offsets(g.ldb, n0, g.N, tid);
 
     auto fetch = [&](int64_t k0) {
         if constexpr (PACKED) {
             pa.load(reinterpret_cast<const uint16_t*>(g.A), g.plane_a, g.lda, m0, k0, tid);
             pb.load(reinterpret_cast<const uint16_t*>(g.B), g.plane_b, g.ldb, n0, k0, tid);
         } else {
-            pa.load(g.A, g.lda, m0, k0, Ra, Ca, g.vec_a, tid);
-            pb.load(g.B, g.ldb, n0, k0, Rb, Cb, g.vec_b, tid);
+            pa.load(g.A, g.lda, m0, k0, g.M, g.K, g.vec_a, oa, tid);
+            pb.load(g.B, g.ldb, n0, k0, g.N, g.K, g.vec_b, ob, tid);
         }
     };
     auto pack = [&](int buf) {

@@ -8,6 +8,41 @@
 
 namespace mg {
 
+// 16-byte access of bytes at any address.
+typedef uint32_t uintx4 __attribute__((ext_vector_type(4)));
+typedef uintx4 uintx4u __attribute__((aligned(1)));
+
+// The byte forms of edge_load and edge_fix (common.h): bytes c .. c+15 of row
+// r of a block of a byte matrix (src: the block's first byte), where any may
+// lie outside; those read 0.
+MG_DEVICE uintx4 edge_load_bytes(const uint8_t* __restrict__ src, int64_t ld, int r, int c, Valid b)
+{
+    const uint8_t* __restrict__ p = src + min(r, b.rows - 1) * ld;
+    if (b.wide) return *reinterpret_cast<const uintx4u*>(p + min(c, b.cols - 16));   // uniform
+    uintx4 w = {0, 0, 0, 0};
+#pragma unroll
+    for (int e = 0; e < 16; ++e) w[e >> 2] |= uint32_t(p[min(c + e, b.cols - 1)]) << (8 * (e & 3));
+    return w;
+}
+
+MG_DEVICE uintx4 edge_fix_bytes(uintx4 w, int r, int c, Valid v)
+{
+    const int left = max(0, min(16, v.cols - c));   // valid columns of the chunk
+    const int keep = r < v.rows ? left : 0;
+    const int sh = v.wide ? 16 - left : 0;          // how far the chunk was moved left
+    uintx4 x = w;
+    if (sh & 8) x = uintx4{x[2], x[3], 0, 0};
+    if (sh & 4) x = uintx4{x[1], x[2], x[3], 0};
+    const int b = 8 * (sh & 3);
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+        const uint64_t pair = (uint64_t(d < 3 ? x[d + 1] : 0u) << 32) | x[d];
+        const int n = keep - 4 * d;   // valid bytes of this word
+        x[d] = uint32_t(pair >> b) & (n >= 4 ? 0xffffffffu : n <= 0 ? 0u : (1u << (8 * n)) - 1u);
+    }
+    return x;
+}
+
 template <int ROWS, int NT, int LDR>
 struct BytePanel {
     static constexpr int CHUNKS = ROWS * 128 / 16;

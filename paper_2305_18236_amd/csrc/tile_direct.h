@@ -35,13 +35,11 @@ namespace mg {
 // read 0 (both operands are zero-padded along K, Section 3.1's remainder rule).
 template <bool KCONTIG>
 MG_DEVICE floatx4 direct_fetch(const float* __restrict__ src, int64_t ld, int64_t r, int64_t k,
-                               int64_t R, int64_t Kd, bool vec, bool interior)
+                               int64_t R, int64_t Kd, bool interior)
 {
     if (interior) {
         if (KCONTIG) {
-            if (vec) return *reinterpret_cast<const floatx4*>(src + r * ld + k);
-            const float* p = src + r * ld + k;
-            return floatx4{p[0], p[1], p[2], p[3]};
+            return *reinterpret_cast<const floatx4u*>(src + r * ld + k);
         }
         const float* p = src + k * ld + r;
         return floatx4{p[0], p[ld], p[2 * ld], p[3 * ld]};
@@ -87,10 +85,10 @@ MG_DEVICE void direct_tile(const GemmArgs& g, int tm, int tn)
         const bool kin = k0 + 8 <= g.K;
 #pragma unroll
         for (int i = 0; i < V; ++i)
-            a[i] = direct_fetch<A_KCONTIG>(g.A, g.lda, mw + 32 * i + c, k, g.M, g.K, g.vec_a, kin && rows_in);
+            a[i] = direct_fetch<A_KCONTIG>(g.A, g.lda, mw + 32 * i + c, k, g.M, g.K, kin && rows_in);
 #pragma unroll
         for (int j = 0; j < H; ++j)
-            b[j] = direct_fetch<B_KCONTIG>(g.B, g.ldb, nw + 32 * j + c, k, g.N, g.K, g.vec_b, kin && cols_in);
+            b[j] = direct_fetch<B_KCONTIG>(g.B, g.ldb, nw + 32 * j + c, k, g.N, g.K, kin && cols_in);
     };
 
     const int64_t nchunks = (g.K + 7) / 8;

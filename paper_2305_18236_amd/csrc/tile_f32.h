@@ -61,53 +61,99 @@ MG_DEVICE constexpr int panel_swizzle(int k)
 // ---------------------------------------------------------------------------
 // Global -> register staging of one panel, in the stored layout.
 //
-// The stored panel is SR x SC floats (SR stored rows, SC stored columns, SC a
-// multiple of 4) starting at (r0, c0) of a stored matrix with R x Cn valid
-// entries and row stride ld.  Thread t fetches chunks q = t + s*NT, each four
-// consecutive stored columns of one stored row.  Out-of-range entries read 0.
-template <int SR, int SC, int NT>
+// The panel holds B rows or columns (m or n, from mn0) of the operand and BK
+// values of k (from k0), of a matrix stored with row stride ld; MN and K are
+// its valid extents.  KMAJOR_SRC: the stored rows are k, the stored columns m
+// or n; else the other way round.  Thread t fetches chunks q = t + s*NT, each
+// four consecutive stored columns of one stored row.
+//
+// Where a panel overhangs the matrix in m or n its lanes read in-range
+// elements instead, by clamped offsets: they feed rows or columns of C that
+// are never stored, so nothing has to be cleared and edge tiles run the same
+// loads as interior ones.  (A k-major chunk that straddles the last column is
+// read whole, up to three elements into the next stored row, which exists
+// except for the last row: a panel holding that one takes the edge path.)
+// Only K overhang must read 0: the last, partial panel, by edge_load.
+// The offsets are the same for every panel and are computed once per tile.
+// Measured with operands of odd row stride, which took element loads with a
+// branch each before: 1531 x 2047 x 1021 TN 98.8 -> 61.4 us.
+template <int B, int BK, int NT, bool KMAJOR_SRC>
 struct PanelLoader {
-    static constexpr int CHUNKS = SR * SC / 4;
+    static constexpr int SC = KMAJOR_SRC ? B : BK;   // stored columns of the panel
+    static constexpr int CHUNKS = B * BK / 4;
     static constexpr int PER_THREAD = (CHUNKS + NT - 1) / NT;
     static_assert(CHUNKS % NT == 0, "panel must split evenly over the workgroup");
 
     floatx4 v[PER_THREAD];
 
-    MG_DEVICE void load(const float* __restrict__ src, int64_t ld, int64_t r0, int64_t c0,
-                        int64_t R, int64_t Cn, bool vec, int tid)
+    // Byte offsets of a thread's chunks from the panel's first element.
+    struct Offsets {
+        uint32_t at[PER_THREAD];
+    };
+
+    MG_DEVICE static Offsets offsets(int64_t ld, int64_t mn0, int64_t MN, int tid)
     {
-        // Wave-uniform test: an interior panel with 16-byte access takes the
-        // branch-free path, so all its loads are in flight at once; edge
-        // panels take the guarded path.
-        if (vec && r0 + SR <= R && c0 + SC <= Cn) {
-            // uniform base + 32-bit per-lane offset (vec guarantees it fits)
-            const float* __restrict__ base = src + r0 * ld + c0;
-            const uint32_t ld32 = uint32_t(ld);
+        const uint32_t ld32 = uint32_t(ld);
+        // the last stored column chunk (row) that holds a valid element
+        const uint32_t last = KMAJOR_SRC ? uint32_t(min(int64_t(B - 4), (MN - 1 - mn0) & ~int64_t(3)))
+                                         : uint32_t(min(int64_t(B - 1), MN - 1 - mn0));
+        Offsets o;
 #pragma unroll
-            for (int s = 0; s < PER_THREAD; ++s) {
-                const int q = tid + s * NT;
-                const uint32_t r = q / (SC / 4), c = (q % (SC / 4)) * 4;
-                v[s] = load16(base, (r * ld32 + c) * 4u);
-            }
+        for (int s = 0; s < PER_THREAD; ++s) {
+            const int q = tid + s * NT;
+            const uint32_t r = q / (SC / 4), c = (q % (SC / 4)) * 4;
+            o.at[s] = KMAJOR_SRC ? (r * ld32 + min(c, last)) * 4u : (min(r, last) * ld32 + c) * 4u;
+        }
+        return o;
+    }
+
+    // The values of k a panel at mn0 needs in the matrix to be loaded whole.
+    MG_DEVICE static int need(int64_t mn0, int64_t MN)
+    {
+        return KMAJOR_SRC && mn0 + B > MN && (MN & 3) != 0 ? BK + 1 : BK;
+    }
+
+    MG_DEVICE static int64_t first(int64_t ld, int64_t mn0, int64_t k0)
+    {
+        return KMAJOR_SRC ? k0 * ld + mn0 : mn0 * ld + k0;
+    }
+
+    // A panel that is loaded whole; o = offsets(ld, mn0, ...).
+    MG_DEVICE void load_whole(const float* __restrict__ src, int64_t ld, int64_t mn0, int64_t k0, const Offsets& o)
+    {
+        const float* __restrict__ base = src + first(ld, mn0, k0);
+#pragma unroll
+        for (int s = 0; s < PER_THREAD; ++s) v[s] = load16(base, o.at[s]);
+    }
+
+    // Any panel.
+    MG_DEVICE void load(const float* __restrict__ src, int64_t ld, int64_t mn0, int64_t k0, int64_t MN, int64_t K,
+                        bool vec, int tid)
+    {
+        // (opaque: these addresses are not kept in registers over the K loop)
+        int t = tid;
+        asm volatile("" : "+v"(t));
+        if (vec && k0 + need(mn0, MN) <= K) {   // wave-uniform
+            load_whole(src, ld, mn0, k0, offsets(ld, mn0, MN, t));
         } else {
+            auto row = [&](int s) { return (t + s * NT) / (SC / 4); };
+            auto col = [&](int s) { return ((t + s * NT) % (SC / 4)) * 4; };
+            const Valid b = KMAJOR_SRC ? valid_part(k0, mn0, K, MN, 4) : valid_part(mn0, k0, MN, K, 4);
+            const float* __restrict__ base = src + first(ld, mn0, k0);
 #pragma unroll
-            for (int s = 0; s < PER_THREAD; ++s) {
-                const int q = tid + s * NT;
-                const int r = q / (SC / 4), c = (q % (SC / 4)) * 4;
-                v[s] = fetch4_guarded(src, ld, r0 + r, c0 + c, R, Cn, vec);
-            }
+            for (int s = 0; s < PER_THREAD; ++s) v[s] = edge_load(base, ld, row(s), col(s), b);
+#pragma unroll
+            for (int s = 0; s < PER_THREAD; ++s) v[s] = edge_fix(v[s], row(s), col(s), b);
         }
     }
 
     // Write into a k-major LDS panel with row length L (floats), swizzled by
-    // panel_swizzle.  kmajor_src: the stored rows are k (stored columns are m
-    // or n), so a chunk is four consecutive m/n of one k row and is written as
+    // panel_swizzle.  KMAJOR_SRC: a chunk is four consecutive m/n of one k row and is written as
     // one 16-byte store.  Otherwise the stored rows are m/n and a chunk is four
     // consecutive k of one m/n: it is transposed into four 4-byte stores.
-    template <bool KMAJOR_SRC, int L>
+    template <int L>
     MG_DEVICE void store(float* lds, int tid) const
     {
-        constexpr int BK = KMAJOR_SRC ? SR : SC;
 #pragma unroll
         for (int s = 0; s < PER_THREAD; ++s) {
             const int q = tid + s * NT;
@@ -183,7 +229,7 @@ MG_DEVICE void sgemm_tile(const GemmArgs& g, int tm, int tn, float* smem)
     static_assert(BK % 2 == 0, "BK must be a multiple of the MFMA depth");
 
     // K group of this wave (uniform across the wave) and its LDS buffers
-    const int grp = KG > 1 ? int(threadIdx.x) / NT : 0;
+    const int grp = KG > 1 ? __builtin_amdgcn_readfirstlane(int(threadIdx.x) / NT) : 0;
     float* gsmem = smem + grp * (2 * BK * (BM + BN));
     float (*As)[BK * BM] = reinterpret_cast<float (*)[BK * BM]>(gsmem);
     float (*Bs)[BK * BN] = reinterpret_cast<float (*)[BK * BN]>(gsmem + 2 * BK * BM);
@@ -199,34 +245,40 @@ MG_DEVICE void sgemm_tile(const GemmArgs& g, int tm, int tn, float* smem)
     const int64_t m0 = int64_t(tm) * BM;
     const int64_t n0 = int64_t(tn) * BN;
 
-    // Stored panels: A is M x K ('N') or K x M ('T'); B is K x N ('N') or N x K ('T').
-    using LA = PanelLoader<TA ? BK : BM, TA ? BM : BK, NT>;
-    using LB = PanelLoader<TB ? BN : BK, TB ? BK : BN, NT>;
+    // A is stored M x K ('N') or K x M ('T'); B is stored K x N ('N') or N x K ('T').
+    using LA = PanelLoader<BM, BK, NT, TA>;
+    using LB = PanelLoader<BN, BK, NT, !TB>;
     LA la[DEEP ? 2 : 1];
     LB lb[DEEP ? 2 : 1];
-    const int64_t Ra = TA ? g.K : g.M, Ca = TA ? g.M : g.K;
-    const int64_t Rb = TB ? g.N : g.K, Cb = TB ? g.K : g.N;
+    typename LA::Offsets oa = LA::offsets(g.lda, m0, g.M, tid);
+    typename LB::Offsets ob = LB::offsets(g.ldb, n0, g.N, tid);
 
-    // Panel p of the K loop: segment p / nk (SYR2K's second product swaps
-    // the operands), k0 = (p % nk) * BK.
+    // Panel p of the K loop: segment p / nk, k0 = (p % nk) * BK.  SYR2K's
+    // second product (segment 1) takes B as the left operand and A as the
+    // right one.
     const int nk = int((g.K + BK - 1) / BK);
+    // The first `nwhole` panels of a segment are loaded whole on both sides.
+    const int64_t spare = g.K - max(LA::need(m0, g.M), LB::need(n0, g.N));
+    const int nwhole = g.vec_a && g.vec_b && spare >= 0 ? int(spare / BK) + 1 : 0;
     // set: the staging set (a compile-time constant, so the sets stay in
-    // registers)
-    auto fetch = [&](int p, auto set) {
+    // registers); quick: panel p is loaded whole and oa, ob are its segment's
+    auto fetch = [&](int p, auto set, auto quick) {
         const bool swap = SYR2K && p >= nk;
         const int64_t k0 = int64_t(swap ? p - nk : p) * BK;
         const float* __restrict__ xa = swap ? g.B : g.A;
         const float* __restrict__ xb = swap ? g.A : g.B;
         const int64_t lxa = swap ? g.ldb : g.lda, lxb = swap ? g.lda : g.ldb;
-        const bool va = swap ? g.vec_b : g.vec_a, vb = swap ? g.vec_a : g.vec_b;
-        if (TA) la[set].load(xa, lxa, k0, m0, Ra, Ca, va, tid);
-        else    la[set].load(xa, lxa, m0, k0, Ra, Ca, va, tid);
-        if (TB) lb[set].load(xb, lxb, n0, k0, Rb, Cb, vb, tid);
-        else    lb[set].load(xb, lxb, k0, n0, Rb, Cb, vb, tid);
+        if constexpr (decltype(quick)::value) {
+            la[set].load_whole(xa, lxa, m0, k0, oa);
+            lb[set].load_whole(xb, lxb, n0, k0, ob);
+        } else {
+            la[set].load(xa, lxa, m0, k0, g.M, g.K, swap ? g.vec_b : g.vec_a, tid);
+            lb[set].load(xb, lxb, n0, k0, g.N, g.K, swap ? g.vec_a : g.vec_b, tid);
+        }
     };
     auto pack = [&](int buf, auto set) {
-        la[set].template store<TA, BM>(As[buf], tid);
-        lb[set].template store<!TB, BN>(Bs[buf], tid);
+        la[set].template store<BM>(As[buf], tid);
+        lb[set].template store<BN>(Bs[buf], tid);
     };
     using Set0 = std::integral_constant<int, 0>;
     using Set1 = std::integral_constant<int, DEEP ? 1 : 0>;
@@ -247,39 +299,38 @@ MG_DEVICE void sgemm_tile(const GemmArgs& g, int tm, int tn, float* smem)
         p0 = int(blockIdx.y * g.k_chunk);
         p1 = min(p1, int(p0 + g.k_chunk));
     }
-    // This group's panels: p0 + grp, then every KG-th.  With KG > 1 the
-    // loop below indexes them by their position i = 0, 1, ... in the
-    // group's sequence and the groups run the same number of iterations
-    // (a group past its last panel only joins the barriers).
-    p0 += grp;
-    const int step = KG;
-    // Panel p is staged in set ((p - p0) / KG) & 1 (DEEP) or set 0, and
-    // multiplied from LDS buffer ((p - p0) / KG) & 1 of the group.
-    if (p0 < p1) {
-        fetch(p0, Set0{});
+    // A group's panels are p0 + grp + i * KG, i = 0, 1, ...; panel i is staged
+    // in set i & 1 (DEEP) or set 0 and multiplied from the group's LDS buffer
+    // i & 1.  Every group runs the iterations of group 0, which has the most
+    // panels (a group past its last panel only joins the barriers).
+    auto panel_of = [&](int i) { return p0 + grp + i * KG; };
+    const int iters = p0 < p1 ? (p1 - p0 + KG - 1) / KG : 0;
+    using No = std::integral_constant<bool, false>;
+    using Yes = std::integral_constant<bool, true>;
+    if (panel_of(0) < p1) {
+        fetch(panel_of(0), Set0{}, No{});
         pack(0, Set0{});
-        if (DEEP && p0 + step < p1) fetch(p0 + step, Set1{});
+        if (DEEP && panel_of(1) < p1) fetch(panel_of(1), Set1{}, No{});
     }
     __syncthreads();
 
     constexpr int STEPS = BK / 2;          // MFMA k-steps per panel
     constexpr int PACK_AT = STEPS / 2;     // the next panel is packed half-way
-    // One panel: LDS buffer cur holds panel kt.  DEEP: fetch panel kt + 2
-    // into set_cur (its panel kt went to LDS one iteration ago) and pack
-    // panel kt + 1 from set_next; otherwise fetch panel kt + 1 into the one
-    // set and pack it half-way.
-    auto panel = [&](int kt, int cur, auto set_cur, auto set_next) {
+    constexpr int AHEAD = DEEP ? 2 : 1;    // panels between a fetch and its use
+    // Panel i, in LDS buffer cur: fetch panel i + AHEAD into set_cur (DEEP: its
+    // panel i went to LDS one iteration ago), and pack panel i + 1 from
+    // set_next half-way.
+    auto panel = [&](int i, int cur, auto set_cur, auto set_next, auto quick) {
         using SetNext = decltype(set_next);
-        using SetCur = decltype(set_cur);
-        if (KG > 1 && kt >= p1) {
-            // this group has no panel left: only the barrier
-            __syncthreads();
-            return;
-        }
-        if (DEEP) {
-            if (kt + 2 * step < p1) fetch(kt + 2 * step, SetCur{});
+        if constexpr (decltype(quick)::value) {
+            fetch(panel_of(i + AHEAD), set_cur, quick);
         } else {
-            if (kt + step < p1) fetch(kt + step, SetCur{});
+            if (KG > 1 && panel_of(i) >= p1) {
+                // this group has no panel left: only the barrier
+                __syncthreads();
+                return;
+            }
+            if (panel_of(i + AHEAD) < p1) fetch(panel_of(i + AHEAD), set_cur, quick);
         }
 
         const float* a_rows = As[cur] + h * BM;
@@ -303,7 +354,7 @@ MG_DEVICE void sgemm_tile(const GemmArgs& g, int tm, int tn, float* smem)
                 lds_read<H>(b_at(s + 1), bn);
             }
             if (s == PACK_AT) {
-                // Pack panel kt + 1 into the other LDS buffer (last read
+                // Pack panel i + 1 into the other LDS buffer (last read
                 // before the previous barrier).  On the last panel this
                 // rewrites stale data nobody reads.
                 pack(cur ^ 1, SetNext{});
@@ -322,18 +373,37 @@ MG_DEVICE void sgemm_tile(const GemmArgs& g, int tm, int tn, float* smem)
         }
         __syncthreads();
     };
-    if constexpr (KG > 1) {
-        // every group runs the iterations of group 0, which has the most panels
-        const int base = p0 - grp;
-        const int iters = base < p1 ? (p1 - base + KG - 1) / KG : 0;
-        if constexpr (DEEP) {
-            for (int i = 0; i < iters; i += 2) {
-                panel(p0 + i * step, 0, Set0{}, Set1{});
-                if (i + 1 < iters) panel(p0 + (i + 1) * step, 1, Set1{}, Set0{});
+    // Unrolled by two, so that the staging set of each panel is a compile-time
+    // choice.  While the panels fetched are all loaded whole the loop runs
+    // without a branch, so that a pack waits for its own panel's loads only
+    // and the newer panel's stay in flight: with the choice of how to load
+    // inside the loop the compiler has to wait for all of them, which undid
+    // half of what the second staging set is for (us, before -> after: 8192^3
+    // 7849 -> 7593, 1024^3 24.9 -> 23.4, SYR2K 2048 x 2048 183 -> 180).
+    int i = 0;
+    auto two = [&](auto quick) {
+        panel(i, 0, Set0{}, Set1{}, quick);
+        if (decltype(quick)::value || i + 1 < iters) panel(i + 1, 1, Set1{}, Set0{}, quick);
+        i += 2;
+    };
+    while (i < iters) {
+        // group 0's panel; the last one fetched by two(Yes) is group KG - 1's
+        auto at = [&]() { return p0 + i * KG; };
+        int lim = nwhole;
+        if (SYR2K) {
+            if (at() >= nk) {   // (the offsets are not kept over both segments)
+                int t = tid;
+                asm volatile("" : "+v"(t));
+                oa = LA::offsets(g.ldb, m0, g.M, t);
+                ob = LB::offsets(g.lda, n0, g.N, t);
+                lim = nk + nwhole;
             }
-        } else {
-            for (int i = 0; i < iters; ++i) panel(p0 + i * step, i & 1, Set0{}, Set0{});
+            lim = min(lim, p1);
         }
+        while (at() + (AHEAD + 2) * KG - 1 < lim) two(Yes{});
+        two(No{});
+    }
+    if constexpr (KG > 1) {
         // Add the groups' sums through LDS (free after the loop's last
         // barrier): group q > 0 stores its accumulators in turn, group 0
         // adds them, in the order q = 1, 2, ...
@@ -362,15 +432,6 @@ MG_DEVICE void sgemm_tile(const GemmArgs& g, int tm, int tn, float* smem)
             __syncthreads();
         }
         if (grp != 0) return;
-    } else if constexpr (DEEP) {
-        // unrolled by two so that the staging set of each panel is a
-        // compile-time choice
-        for (int kt = p0; kt < p1; kt += 2) {
-            panel(kt, 0, Set0{}, Set1{});
-            if (kt + 1 < p1) panel(kt + 1, 1, Set1{}, Set0{});
-        }
-    } else {
-        for (int kt = p0; kt < p1; ++kt) panel(kt, (kt - p0) & 1, Set0{}, Set0{});
     }
 
     // Epilogue: C = alpha*acc + beta*C0, once per element.  C0 is read
@@ -383,9 +444,9 @@ MG_DEVICE void sgemm_tile(const GemmArgs& g, int tm, int tn, float* smem)
     auto row_of = [&](int i, int r) { return m0 + wm0 + V * (8 * (r >> 2) + 4 * h + (r & 3)) + i; };
     // columns ncol .. ncol+H-1 all inside the stored triangle
     auto whole = [&](int64_t m) { return UPLO == 0 || (UPLO == 1 ? ncol + H - 1 <= m : ncol >= m); };
-    // one 16-byte (H = 4) or 8-byte (H = 2) access per row: vec_c makes
-    // C and ldc 16-byte aligned and ncol is a multiple of H
-    auto vec_row = [&](int64_t m) { return (H == 4 || H == 2) && g.vec_c && ncol + H - 1 < g.N && whole(m); };
+    // one 16-byte (H = 4) or 8-byte (H = 2) access per row, at any 4-byte
+    // address
+    auto vec_row = [&](int64_t m) { return (H == 4 || H == 2) && ncol + H - 1 < g.N && whole(m); };
     auto inside = [&](int64_t m, int j) {
         return ncol + j < g.N && (UPLO == 0 || (UPLO == 1 ? ncol + j <= m : ncol + j >= m));
     };
@@ -401,18 +462,18 @@ MG_DEVICE void sgemm_tile(const GemmArgs& g, int tm, int tn, float* smem)
                 // Out-of-range rows and columns read a clamped in-range
                 // element that is never stored (nor is anything outside the
                 // triangle), so the loads need no branches.
-                const bool vec = (H == 4 || H == 2) && g.vec_c && ncol + H - 1 < g.N;
+                const bool vec = (H == 4 || H == 2) && ncol + H - 1 < g.N;
 #pragma unroll
                 for (int rr = 0; rr < RB; ++rr) {
                     const int64_t m = row_of(i, r0 + rr);
                     const float* cp = g.C + (m < g.M ? m : g.M - 1) * g.ldc;
                     if (vec) {
                         if constexpr (H == 4) {
-                            const floatx4 v = *reinterpret_cast<const floatx4*>(cp + ncol);
+                            const floatx4 v = *reinterpret_cast<const floatx4u*>(cp + ncol);
 #pragma unroll
                             for (int j = 0; j < H; ++j) c0[rr][j] = v[j];
                         } else if constexpr (H == 2) {
-                            const floatx2 v = *reinterpret_cast<const floatx2*>(cp + ncol);
+                            const floatx2 v = *reinterpret_cast<const floatx2u*>(cp + ncol);
 #pragma unroll
                             for (int j = 0; j < H; ++j) c0[rr][j] = v[j];
                         }
@@ -435,10 +496,10 @@ MG_DEVICE void sgemm_tile(const GemmArgs& g, int tm, int tn, float* smem)
                 if (vec_row(m)) {
                     if constexpr (H == 4) {
                         const floatx4 v = {o[0], o[1], o[2], o[3]};
-                        *reinterpret_cast<floatx4*>(cp) = v;
+                        *reinterpret_cast<floatx4u*>(cp) = v;
                     } else if constexpr (H == 2) {
                         const floatx2 v = {o[0], o[1]};
-                        *reinterpret_cast<floatx2*>(cp) = v;
+                        *reinterpret_cast<floatx2u*>(cp) = v;
                     }
                 } else {
 #pragma unroll

@@ -30,21 +30,17 @@ MG_DEVICE void valu_tile(const GemmArgs& g, int tm, int tn, float* smem)
     const int tx = tid & 15, ty = tid >> 4;
     const int64_t m0 = int64_t(tm) * BM, n0 = int64_t(tn) * BN;
 
-    using LA = PanelLoader<TA ? BK : BM, TA ? BM : BK, NT>;
-    using LB = PanelLoader<TB ? BN : BK, TB ? BK : BN, NT>;
+    using LA = PanelLoader<BM, BK, NT, TA>;
+    using LB = PanelLoader<BN, BK, NT, !TB>;
     LA la;
     LB lb;
-    const int64_t Ra = TA ? g.K : g.M, Ca = TA ? g.M : g.K;
-    const int64_t Rb = TB ? g.N : g.K, Cb = TB ? g.K : g.N;
     auto fetch = [&](int64_t k0) {
-        if (TA) la.load(g.A, g.lda, k0, m0, Ra, Ca, g.vec_a, tid);
-        else    la.load(g.A, g.lda, m0, k0, Ra, Ca, g.vec_a, tid);
-        if (TB) lb.load(g.B, g.ldb, n0, k0, Rb, Cb, g.vec_b, tid);
-        else    lb.load(g.B, g.ldb, k0, n0, Rb, Cb, g.vec_b, tid);
+        la.load(g.A, g.lda, m0, k0, g.M, g.K, g.vec_a, tid);
+        lb.load(g.B, g.ldb, n0, k0, g.N, g.K, g.vec_b, tid);
     };
     auto pack = [&](int buf) {
-        la.template store<TA, BM>(As[buf], tid);
-        lb.template store<!TB, BN>(Bs[buf], tid);
+        la.template store<BM>(As[buf], tid);
+        lb.template store<BN>(Bs[buf], tid);
     };
 
     float acc[8][8];
@@ -102,8 +98,8 @@ MG_DEVICE void valu_tile(const GemmArgs& g, int tm, int tn, float* smem)
 #pragma unroll
             for (int half = 0; half < 2; ++half) {
                 const int64_t n = n0 + half * 64 + tx * 4;
-                if (g.vec_c && n + 3 < g.N) {
-                    c0[i][half] = *reinterpret_cast<const floatx4*>(crow + n);
+                if (n + 3 < g.N) {
+                    c0[i][half] = *reinterpret_cast<const floatx4u*>(crow + n);
                 } else {
 #pragma unroll
                     for (int e = 0; e < 4; ++e) c0[i][half][e] = crow[n + e < g.N ? n + e : g.N - 1];
@@ -124,8 +120,8 @@ MG_DEVICE void valu_tile(const GemmArgs& g, int tm, int tn, float* smem)
 #pragma unroll
             for (int e = 0; e < 4; ++e)
                 o[e] = beta != 0.f ? __builtin_fmaf(alpha, v[e], beta * c0[i][half][e]) : alpha * v[e];
-            if (g.vec_c && n + 3 < g.N) {
-                *reinterpret_cast<floatx4*>(cp) = o;
+            if (n + 3 < g.N) {
+                *reinterpret_cast<floatx4u*>(cp) = o;
             } else {
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
