@@ -70,6 +70,11 @@ const SgemmConfig kSgemmConfigs[] = {
     {19, 128, 128, 32, 32, 64},
     // the 128 x 64 tile over eight 32 x 32 waves with two staging sets
     {20, 128, 64, 32, 32, 32},
+    // 32-row and 32-column tiles for skinny and small outputs, over four,
+    // four and eight K groups of waves
+    {21, 32, 64, 32, 32, 32},
+    {22, 64, 32, 32, 32, 32},
+    {23, 32, 32, 32, 32, 32},
 };
 const int kNumSgemmConfigs = sizeof(kSgemmConfigs) / sizeof(kSgemmConfigs[0]);
 
@@ -97,6 +102,9 @@ hipError_t launch_sgemm(int cfg, bool ta, bool tb, GemmArgs g, hipStream_t strea
     case 18: return launch_sgemm_cfg<128, 128, 32, 64, 32, true>(ta, tb, g, stream);
     case 19: return launch_sgemm_cfg<128, 128, 32, 32, 64, true>(ta, tb, g, stream);
     case 20: return launch_sgemm_cfg<128, 64, 32, 32, 32, true>(ta, tb, g, stream);
+    case 21: return launch_sgemm_cfg<32, 64, 32, 32, 32, true, 4>(ta, tb, g, stream);
+    case 22: return launch_sgemm_cfg<64, 32, 32, 32, 32, true, 4>(ta, tb, g, stream);
+    case 23: return launch_sgemm_cfg<32, 32, 32, 32, 32, true, 8>(ta, tb, g, stream);
     default: return hipErrorInvalidValue;
     }
 }

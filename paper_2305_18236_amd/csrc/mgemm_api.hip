@@ -5,6 +5,7 @@
 #include <algorithm>
 #include <atomic>
 #include <climits>
+#include <cmath>
 #include <cstdint>
 #include <cstdio>
 #include <cstring>
@@ -458,6 +459,85 @@ Fp32Plan fp32_plan(int64_t M, int64_t N, int64_t K, int pick, bool split_ok)
     return best;
 }
 
+// ---- FP32 outputs that are small (fewer than half a 64 x 64 tile per compute
+// unit) or skinny (under 256 rows or columns).  The ladder looks for the
+// largest tile that fills the compute units, which here multiplies mostly
+// padding (32 x 8192 x 8192 ran 256 x 256 tiles in eight K ranges: 258 us
+// where reading B takes 57), so these compare the tiles that fit them by a
+// time model: the 64 x 64 tile with one and two K groups (12, 15), the tiles
+// with 32 rows or columns (21, 22, 23) and the 128 x 128 tile (18), in 1 to
+// 16 K ranges.  A compute unit runs its workgroups in rounds of `occ`; a round
+// takes c0 plus the longer of its K iterations at `lat` each and its matrix
+// work at the rate `eff` of the peak; the product is bound below by reading
+// the operands (3.6 TB/s, from HBM) and the tiles' panels (6.3 TB/s, through
+// L2); a split adds a reduction.  The constants are fitted to 125 random
+// shapes with 20-40 plans each (device time): the plan it picks is within 1.1 %
+// of the best one in geometric mean, at most 10 %, and 22 % faster than the
+// ladder's (us, ladder -> model: 32 x 8192 x 8192 NT 258 -> 65, 7 x 4096 x
+// 4096 72 -> 20, 128 x 8192 x 8192 260 -> 155, 6939 x 27 x 2293 32 -> 27,
+// 28 x 218 x 514 13.1 -> 9.7).
+struct SmallTile {
+    int cfg, bm, bn, kg, occ;
+    float lat, c0, eff;   // us, us, fraction of the matrix-core rate
+};
+const SmallTile kSmallTiles[] = {
+    {12, 64, 64, 1, 4, 0.628f, 3.38f, 0.772f}, {15, 64, 64, 2, 2, 0.562f, 3.84f, 0.756f},
+    {21, 32, 64, 4, 1, 0.485f, 4.25f, 0.637f}, {22, 64, 32, 4, 1, 0.485f, 4.25f, 0.637f},
+    {23, 32, 32, 8, 1, 1.658f, 4.25f, 0.905f}, {18, 128, 128, 1, 2, 0.601f, 4.35f, 0.870f},
+};
+
+bool small_or_skinny(int64_t M, int64_t N, int64_t cus)
+{
+    return std::min(M, N) < 256 || 2 * tiles(M, N, 64, 64) <= cus;
+}
+
+float small_tile_us(const SmallTile& c, float M, float N, float K, float s, float chunk, float cus)
+{
+    const float panels = std::ceil(chunk / 32.f);
+    const float count = std::ceil(M / float(c.bm)) * std::ceil(N / float(c.bn));
+    const float per_cu = std::ceil(count * s / cus), full = std::floor(per_cu / float(c.occ));
+    const float iters = std::ceil(panels / float(c.kg)) * c.lat;
+    // a 32 x 32 x 32 product takes a compute unit 0.107 us at the peak rate
+    const float work = panels * float(c.bm * c.bn) * (0.107f / 1024.f) / c.eff;
+    const float rem = per_cu - full * float(c.occ);
+    float t = full * (c.c0 + std::max(iters, float(c.occ) * work));
+    if (rem > 0.f) t += c.c0 + std::max(iters, rem * work);
+    t = std::max({t, 4.f * (M * K + K * N + M * N) / 3.616e6f, 4.f * count * float(c.bm + c.bn) * K / 6.33e6f});
+    if (s > 1.f) t += 3.19f + 4.f * (s + 1.f) * M * N / 7.34e6f;
+    return t;
+}
+
+Fp32Plan small_plan(int64_t M, int64_t N, int64_t K, bool split_ok)
+{
+    // A call asks for the plan of its shape several times (workspace size,
+    // configuration, split): the last one of the thread is kept.  It depends
+    // on nothing but these values.
+    struct Memo {
+        int64_t M, N, K, cus;
+        bool split_ok;
+        Fp32Plan plan;
+    };
+    static thread_local Memo memo{-1, -1, -1, -1, false, {0, 1}};
+    const int64_t cus = device_cus();
+    if (memo.M == M && memo.N == N && memo.K == K && memo.cus == cus && memo.split_ok == split_ok) return memo.plan;
+    Fp32Plan best{15, 1};
+    float best_us = 1e30f;
+    const int64_t most = split_ok ? std::min<int64_t>(kMaxSplits, K / kSplitGrain) : 1;
+    for (int64_t s = 1; s <= std::max<int64_t>(most, 1); ++s) {
+        const int64_t chunk = s > 1 ? round_up((K + s - 1) / s, kSplitGrain) : K;
+        if (s > 1 && (K + chunk - 1) / chunk != s) continue;   // cut into fewer ranges: weighed there
+        for (const SmallTile& c : kSmallTiles) {
+            const float us = small_tile_us(c, float(M), float(N), float(K), float(s), float(chunk), float(cus));
+            if (us < best_us) {
+                best = Fp32Plan{c.cfg, int(s)};
+                best_us = us;
+            }
+        }
+    }
+    memo = Memo{M, N, K, cus, split_ok, best};
+    return best;
+}
+
 // The 64 x 64 FP32 tile with two register staging sets (12) replaces the
 // one-set form (3) wherever the rule picks that tile: measured (NN, beta
 // 0.5, % of the FP32 peak) 1024^3 46.2 -> 50.9, 1536^3 in four K ranges
@@ -560,6 +640,8 @@ int choose_config(int path, int64_t M, int64_t N, int64_t K, bool split_ok)
     // paper finds for small matrices (measured: 0.84x the packed time at 16^3,
     // 0.95x at 32^3, even at 64^3, packing ahead from 128^3 on).
     if (path == MG_PATH_FP32 && std::max({M, N, K}) <= 32) return 8;
+    if (path == MG_PATH_FP32 && M > 0 && N > 0 && K > 0 && small_or_skinny(M, N, cus))
+        return small_plan(M, N, K, split_ok).cfg;
     const int pick = ladder_choice(path, M, N, K, cus, split_ok);
     // BF16 and FP16 (one product per step) run the 128 x 128 tile as eight
     // 32 x 64 waves (9): two waves per SIMD where configuration 2 has one,
@@ -673,8 +755,10 @@ SplitPlan split_plan(int path, int cfg, int64_t M, int64_t N, int64_t K, bool sp
         if (e != nullptr && e->cfg == cfg && e->splits > 0) s = e->splits;
     }
     if (s < 0 && path == MG_PATH_FP32) {
-        // the K ranges the round plan chose with this configuration
-        const Fp32Plan fp = fp32_plan(M, N, K, ladder_choice(path, M, N, K, device_cus(), true), true);
+        // the K ranges the rule chose with this configuration
+        const Fp32Plan fp = small_or_skinny(M, N, device_cus())
+                                ? small_plan(M, N, K, true)
+                                : fp32_plan(M, N, K, ladder_choice(path, M, N, K, device_cus(), true), true);
         if (fp.cfg == cfg || (fp.cfg == 3 && (cfg == 12 || cfg == 15)) || (fp.cfg == 5 && cfg == 17) ||
             (fp.cfg == 0 && cfg == 18) || (fp.cfg == 4 && cfg == 20))
             s = fp.splits;

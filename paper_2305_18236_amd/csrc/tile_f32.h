@@ -51,11 +51,12 @@
 
 namespace mg {
 
-template <int BK>
+// L: the panel's row length; rows of 32 swizzle over their 32 banks.
+template <int BK, int L = 64>
 MG_DEVICE constexpr int panel_swizzle(int k)
 {
     constexpr int NC = BK / 4;   // 4-float chunks per stored row of a transposing panel
-    return ((k >> 2) % NC) * (64 / NC);
+    return ((k >> 2) % NC) * ((L < 64 ? L : 64) / NC);
 }
 
 // ---------------------------------------------------------------------------
@@ -160,9 +161,9 @@ struct PanelLoader {
             const int r = q / (SC / 4);
             const int c = (q % (SC / 4)) * 4;
             if (KMAJOR_SRC) {
-                *reinterpret_cast<floatx4*>(lds + r * L + (c ^ panel_swizzle<BK>(r))) = v[s];
+                *reinterpret_cast<floatx4*>(lds + r * L + (c ^ panel_swizzle<BK, L>(r))) = v[s];
             } else {
-                const int m = r ^ panel_swizzle<BK>(c);   // same for k = c .. c+3
+                const int m = r ^ panel_swizzle<BK, L>(c);   // same for k = c .. c+3
                 lds[(c + 0) * L + m] = v[s][0];
                 lds[(c + 1) * L + m] = v[s][1];
                 lds[(c + 2) * L + m] = v[s][2];
@@ -338,8 +339,8 @@ MG_DEVICE void sgemm_tile(const GemmArgs& g, int tm, int tn, float* smem)
         const int am = wm0 + V * c, bnn = wn0 + H * c;
         // Rows k = 2s and 2s+1 share their swizzle (it changes with k/4), so
         // the swizzle of a step is a compile-time constant.
-        auto a_at = [&](int s) { return a_rows + 2 * s * BM + (am ^ panel_swizzle<BK>(2 * s)); };
-        auto b_at = [&](int s) { return b_rows + 2 * s * BN + (bnn ^ panel_swizzle<BK>(2 * s)); };
+        auto a_at = [&](int s) { return a_rows + 2 * s * BM + (am ^ panel_swizzle<BK, BM>(2 * s)); };
+        auto b_at = [&](int s) { return b_rows + 2 * s * BN + (bnn ^ panel_swizzle<BK, BN>(2 * s)); };
         // Software pipeline: the fragments of step s+1 are read from LDS
         // before the MFMAs of step s are issued, into separate registers, so
         // LDS latency hides behind the matrix core.
