@@ -29,6 +29,8 @@
 //   q:      Rp x Kp bytes, row r holds E4M3 codes of op(X)[r][0..Kp)
 //   scales: (Rp/128) x (Kp/128) E8M0 bytes, row-major
 //   Rp = roundup(R, 256), Kp = roundup(K, 128).
+#include <type_traits>
+
 #include "common.h"
 #include "kernels.h"
 #include "tile_bytes.h"
@@ -556,6 +558,180 @@ static hipError_t launch_fp8_direct(Fp8Args g, hipStream_t stream)
     return hipGetLastError();
 }
 
+// Few rows (a decode step: tens of rows of activations against weights packed
+// once): reading the weights bounds it, so the work is cut to keep as many
+// bytes in flight on as many compute units as it can.  A workgroup owns a BM x
+// BN tile; each of its NW waves takes every NW-th 128-deep K panel through its
+// own ring of two LDS stages.  A stage is filled by direct copies, awaited by
+// its wave alone, read into registers whole and at once refilled, two panels
+// ahead, so the K loop has no barrier.  At the end the waves' partial tiles
+// are added through LDS in order of the wave, and every thread stores its
+// share of C.
+// GEMM only, us, 64 x 64 tiles of gemm_fp8_kernel -> the best of the three
+// tiles: 1 x 8192 x 8192 34.6 -> 12.5 (67 MB: 5.4 TB/s), 64 x 8192 x 8192
+// 35.6 -> 14.8, 128 x 8192 x 8192 35.8 -> 18.3, 64 x 1024 x 8192 34.1 -> 7.9,
+// 384 x 384 x 4096 18.8 -> 5.6.  A third stage, and 128 x 32 tiles over four
+// waves, were no faster anywhere.
+template <int BM, int BN, int NW>
+__global__ __launch_bounds__(NW * 64) void gemm_fp8_skinny_kernel(Fp8Args g)
+{
+    constexpr int NS = 2;                           // stages of a wave's ring
+    constexpr int V = BM / 32, H = BN / 32;
+    constexpr int STAGE = (BM + BN) * 128;          // bytes of one wave's stage
+    constexpr int COPIES = (BM + BN) / 8;           // copy instructions per stage
+    static_assert((NS - 1) * COPIES < 64, "the wait counts the copies in flight");
+    // one array per stage, so that the compiler can tell the copies into one
+    // from the reads of another
+    __shared__ __attribute__((aligned(1024))) uint8_t S0[NW * STAGE];
+    __shared__ __attribute__((aligned(1024))) uint8_t S1[NW * STAGE];
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int c = lane & 31, h = lane >> 5;
+    int tm, tn;
+    tile_of(blockIdx.x, g.tiles_m, g.tiles_n, g.group_m, g.remap, tm, tn);
+    const int64_t m0 = int64_t(tm) * BM, n0 = int64_t(tn) * BN;
+    const uint8_t* __restrict__ qa = g.qA + m0 * g.ldq;
+    const uint8_t* __restrict__ qb = g.qB + n0 * g.ldq;
+    const uint32_t ld32 = uint32_t(g.ldq);
+    const uint8_t* __restrict__ sA = g.sA + (m0 / 128) * g.lds;
+    const uint8_t* __restrict__ sB = g.sB + (n0 / 128) * g.lds;
+
+    floatx16 acc[V][H];
+#pragma unroll
+    for (int i = 0; i < V; ++i)
+#pragma unroll
+        for (int j = 0; j < H; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+    const int nk = int(g.Kp / 128);
+    // this wave's panels: wave, wave + NW, ...
+    const int n = nk > wave ? (nk - wave + NW - 1) / NW : 0;
+    auto copy = [&](uint8_t* S, int i) {
+        uint8_t* L = S + wave * STAGE;
+        const uint32_t k0 = uint32_t(wave + i * NW) * 128u;
+        direct_copy<BM, 1>(qa, ld32, k0, L, 0, lane);
+        direct_copy<BN, 1>(qb, ld32, k0, L + BM * 128, 0, lane);
+    };
+    // (one 16-byte vector load each: as a struct of four words some of the
+    // reads lose what tells them from the copies in flight, and wait for all)
+    auto frag = [&](const uint8_t* L, int row, int s) {
+        const int g0 = 4 * s + 2 * h;
+        const uintx4 lo = *reinterpret_cast<const uintx4*>(L + row * 128 + 16 * (g0 ^ direct_swz(row)));
+        const uintx4 hi = *reinterpret_cast<const uintx4*>(L + row * 128 + 16 * ((g0 + 1) ^ direct_swz(row)));
+        return intx8{int(lo[0]), int(lo[1]), int(lo[2]), int(lo[3]), int(hi[0]), int(hi[1]), int(hi[2]), int(hi[3])};
+    };
+    // Scale bytes of 60 panels (a multiple of NS) from panel `at` on, one per
+    // lane.
+    int scale_a = 127, scale_b = 127;
+    auto scales = [&](int at) {
+        const int p = min(wave + (at + lane) * NW, nk - 1);
+        scale_a = sA[p];
+        scale_b = sB[p];
+    };
+    // (awaited here: with the loads pending into the K loop the compiler
+    // waits for everything at its head)
+    auto scales_here = [&]() { asm volatile("" : "+v"(scale_a), "+v"(scale_b)); };
+    // Panel i (its scales in lane `slot`) in stage S.  MORE: NS - 1 newer
+    // panels are in flight and may stay so, and panel i + NS exists.
+    auto step = [&](int i, int slot, uint8_t* S, auto more) {
+        constexpr bool MORE = decltype(more)::value;
+        constexpr int FLY = MORE ? (NS - 1) * COPIES : 0;
+        __builtin_amdgcn_s_waitcnt(0x0f70 | (FLY & 15) | (FLY >> 4 << 14));   // vmcnt(FLY)
+        const uint8_t* L = S + wave * STAGE;
+        intx8 a[2][V], b[2][H];
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+#pragma unroll
+            for (int v = 0; v < V; ++v) a[s][v] = frag(L, 32 * v + c, s);
+#pragma unroll
+            for (int v = 0; v < H; ++v) b[s][v] = frag(L + BM * 128, 32 * v + c, s);
+        }
+        __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0): the stage is read
+        if constexpr (MORE) copy(S, i + NS);
+        const int sa = __builtin_amdgcn_readlane(scale_a, slot), sb = __builtin_amdgcn_readlane(scale_b, slot);
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int v = 0; v < V; ++v)
+#pragma unroll
+                for (int w = 0; w < H; ++w)
+                    acc[v][w] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a[s][v], b[s][w], acc[v][w], 0, 0, 0,
+                                                                                sa, 0, sb);
+    };
+    using Yes = std::integral_constant<bool, true>;
+    using No = std::integral_constant<bool, false>;
+    // NS panels at a time, so that each one's stage is a compile-time choice,
+    // and without a branch while panels remain to be copied (with one the
+    // compiler waits for every copy in flight before each panel).
+    int i = 0, at = 0;
+    scales(0);
+    if (n > 0) copy(S0, 0);
+    if (n > 1) copy(S1, 1);
+    scales_here();
+    for (;;) {
+        const int lim = at + 60;
+        for (; i < lim && i + 2 * NS - 1 < n; i += NS) {
+            step(i, i - at, S0, Yes{});
+            step(i + 1, i + 1 - at, S1, Yes{});
+        }
+        if (i < lim) break;
+        at = i;
+        scales(at);
+        scales_here();
+    }
+    // the last panels, at most 2 NS - 1, some of them not yet copied
+    if (i - at + 2 * NS > 64) {
+        at = i;
+        scales(at);
+        scales_here();
+    }
+#pragma unroll
+    for (int t = 0; t < 2 * NS - 1; ++t) {
+        uint8_t* S = t % NS == 0 ? S0 : S1;
+        if (i + NS < n) step(i, i - at, S, Yes{});
+        else if (i < n) step(i, i - at, S, No{});
+        ++i;
+    }
+    // every wave's reads and copies are done: the stages are free
+    __syncthreads();
+    float* red = reinterpret_cast<float*>(S0);
+    static_assert(NW * BM * BN * 4 <= NW * STAGE, "partial tiles fit a stage");
+#pragma unroll
+    for (int v = 0; v < V; ++v)
+#pragma unroll
+        for (int w = 0; w < H; ++w)
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                red[(wave * BM + 32 * v + 8 * (r >> 2) + 4 * h + (r & 3)) * BN + 32 * w + c] = acc[v][w][r];
+    __syncthreads();
+    const float alpha = g.alpha, beta = g.beta;
+    const int64_t col = n0 + (tid % BN);
+    constexpr int ROWS = NW * 64 / BN;
+#pragma unroll
+    for (int q = 0; q < BM / ROWS; ++q) {
+        const int row = tid / BN + ROWS * q;
+        float x = red[row * BN + (tid % BN)];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) x += red[(w * BM + row) * BN + (tid % BN)];
+        if (m0 + row < g.M && col < g.N) {
+            float* p = g.C + (m0 + row) * g.ldc + col;
+            *p = beta != 0.f ? __builtin_fmaf(alpha, x, beta * *p) : alpha * x;
+        }
+    }
+}
+
+template <int BM, int BN, int NW>
+static hipError_t launch_fp8_skinny(Fp8Args g, hipStream_t stream)
+{
+    g.tiles_m = int((g.M + BM - 1) / BM);
+    g.tiles_n = int((g.N + BN - 1) / BN);
+    hipLaunchKernelGGL((gemm_fp8_skinny_kernel<BM, BN, NW>), dim3(g.tiles_m * g.tiles_n), dim3(NW * 64), 0,
+                       stream, g);
+    return hipGetLastError();
+}
+
 const SgemmConfig kFp8Configs[] = {
     // id, BM, BN, BK, WM, WN
     {0, 256, 256, 128, 128, 128},
@@ -570,6 +746,11 @@ const SgemmConfig kFp8Configs[] = {
     {9, 128, 128, 128, 64, 64},    // as 8, barrier before each panel's last step
     {10, 128, 128, 128, 64, 32},   // as 8 over eight 64 x 32 waves
     {11, 256, 256, 128, 64, 64},   // as 7 over sixteen 64 x 64 waves
+    // few rows: waves that each take their own K panels, without barriers
+    // (eight waves, four, four)
+    {12, 32, 32, 128, 32, 32},
+    {13, 64, 32, 128, 64, 32},
+    {14, 64, 64, 128, 64, 64},
 };
 const int kNumFp8Configs = sizeof(kFp8Configs) / sizeof(kFp8Configs[0]);
 
@@ -588,6 +769,9 @@ hipError_t launch_gemm_fp8(int cfg, Fp8Args g, hipStream_t stream)
     case 9: return launch_fp8_direct<128, 128, 64, 64, true>(g, stream);
     case 10: return launch_fp8_direct<128, 128, 64, 32, false>(g, stream);
     case 11: return launch_fp8_direct<256, 256, 64, 64, false>(g, stream);
+    case 12: return launch_fp8_skinny<32, 32, 8>(g, stream);
+    case 13: return launch_fp8_skinny<64, 32, 4>(g, stream);
+    case 14: return launch_fp8_skinny<64, 64, 4>(g, stream);
     default: return hipErrorInvalidValue;
     }
 }

@@ -578,6 +578,44 @@ int fp32_small_tile(int cfg, int64_t M, int64_t N, int64_t K, int splits, bool s
     return t * s <= cus || (t * s <= 2 * cus && (K + s - 1) / s >= 512) ? 15 : 12;
 }
 
+// FP8 outputs of fewer 256 x 256 tiles than half the compute units: the tile
+// with the least time by a model of each (us; GEMM only, fitted to 22 shapes
+// of 1 to 1024 rows, of which it picks the best in all, and never more than
+// 2 us off).  12, 13 and 14 hold one workgroup per compute unit, so they pay
+// their fixed time every round, and their first round waits for the operands
+// from HBM (6.4 TB/s); the 64 x 64 tile (3) and the 128 x 128 tile (10) hold
+// four and two, whose fixed times overlap.  E.g. 100 x 8192 x 8192: 12 31.0,
+// 13 23.4, 14 17.9, 3 36.0; 200 x 8192 x 1024: 19.2, 16.4, 12.9, 8.7.
+int fp8_small_config(int64_t M, int64_t N, int64_t K, int64_t cus)
+{
+    struct Tile {
+        int cfg, bm, bn, waves;
+        double base, c0, step;   // us: a launch, a round, a K panel of a wave
+    };
+    static const Tile kTiles[] = {
+        {12, 32, 32, 8, 1.0, 1.9, 0.64}, {13, 64, 32, 4, 1.3, 3.0, 0.41}, {14, 64, 64, 4, 0.3, 5.3, 0.49}};
+    auto per_cu = [&](int bm, int bn) { return double((tiles(M, N, bm, bn) + cus - 1) / cus); };
+    const double nk = double((K + 127) / 128);
+    const double hbm = double(M + N) * double(K) / 6.4e6;
+    double best_us = 2.1 + 0.51 * nk + (per_cu(64, 64) - 1) * (1.2 + 0.02 * nk);
+    int best = 3;
+    // (two to a compute unit run as one round)
+    const double us10 = std::ceil(per_cu(128, 128) / 2) * (2.5 + nk * (per_cu(128, 128) > 1 ? 0.78 : 0.68));
+    if (us10 < best_us) {
+        best_us = us10;
+        best = 10;
+    }
+    for (const Tile& t : kTiles) {
+        const double loop = std::ceil(nk / t.waves) * t.step;
+        const double us = t.base + t.c0 + std::max(hbm, loop) + (per_cu(t.bm, t.bn) - 1) * (t.c0 + loop);
+        if (us < best_us) {
+            best_us = us;
+            best = t.cfg;
+        }
+    }
+    return best;
+}
+
 int choose_config(int path, int64_t M, int64_t N, int64_t K, bool split_ok)
 {
     const int64_t cus = device_cus();
@@ -611,8 +649,7 @@ int choose_config(int path, int64_t M, int64_t N, int64_t K, bool split_ok)
         const int64_t n256 = tiles(M, N, 256, 256);
         if (n256 > cus && n256 < 2 * cus && (n256 - cus) * 3 < cus) return 10;
         if (n256 * 2 > cus) return 11;
-        if (tiles(M, N, 128, 128) >= 128) return 10;
-        return 3;
+        return fp8_small_config(M, N, K, cus);
     }
     if (path == MG_CONFIGS_I8) {
         // 256 x 256: panels copied straight into LDS (5): 2255 TOP/s at

@@ -1,4 +1,5 @@
-"""FP32 tiles of 32 rows or columns (configurations 21-23), the plans of small
+"""FP32 tiles of 32 rows or columns (configurations 21-23), the FP8 tiles for few
+rows (configurations 12-14), the plans of small
 and skinny outputs, and odd row strides at every edge of a tile and a K panel.
 
 Integer operands (|x| <= 8): every partial sum stays below 2^24, so FP32 is
@@ -56,3 +57,25 @@ def test_odd_strides_and_edges(gpu, path, tA, tB, M, N, K):
     a 4-element chunk, with NaN-free padding between the rows never stored."""
     a, b = (M if tA == "T" else K), (K if tB == "T" else N)
     run_exact(gpu, M, N, K, tA, tB, path, lda=a + 1, ldb=b + 2, ldc=N + 3)
+
+
+@pytest.mark.parametrize("cfg,waves", [(12, 8), (13, 4), (14, 4)])
+@pytest.mark.parametrize("panels", [1, 2, 3, 4, 5, 59, 60, 61, 64])
+def test_fp8_skinny_tiles_every_ring_state(gpu, cfg, waves, panels):
+    """FP8 tiles whose waves take their own K panels: every count of panels
+    around the ring's fill and around the 60 panels whose scales a wave holds,
+    with whole and ragged last rows of panels, exact on integers."""
+    from paper_2305_18236_amd import _native
+    _native.check(_native.mg_force_config(3, cfg), "mg_force_config")
+    try:
+        for K in {128 * waves * panels, 128 * waves * (panels - 1) + 130}:
+            run_exact(gpu, 33, 70, K, "N", "T", "fp8", ldc=71)
+    finally:
+        _native.mg_force_config(3, -1)
+
+
+@pytest.mark.parametrize("M,N,K", [(1, 1024, 1000), (32, 1030, 4096), (64, 1024, 2500), (65, 2049, 1024),
+                                   (200, 1024, 300), (256, 1500, 2048), (384, 384, 4096)])
+def test_fp8_few_rows(gpu, M, N, K):
+    run_exact(gpu, M, N, K, "N", "T", "fp8")
+    run_exact(gpu, M, N, K, "T", "N", "fp8")
