@@ -31,9 +31,6 @@ struct GemmArgs {
     // offset, and stored rows hold at least one 4-float chunk.  No alignment
     // is asked for: 16-byte global accesses need 4-byte alignment only.
     int vec_a, vec_b;
-    // Pre-packed BF16 operands only: element offset from the hi plane of
-    // op(A) (op(B)^T) to its lo plane.
-    int64_t plane_a, plane_b;
     // Split-K (launched with gridDim.y > 1): workgroup row s of the grid
     // multiplies the K range [s*k_chunk, min(K, (s+1)*k_chunk)) and stores its
     // unscaled partial product at part + s*part_stride (row stride ldp, a

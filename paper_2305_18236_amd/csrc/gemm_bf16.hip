@@ -188,8 +188,15 @@ static hipError_t launch_bf16_cfg(bool ta, bool tb, GemmArgs g, hipStream_t stre
     g.tiles_m = int((g.M + BM - 1) / BM);
     g.tiles_n = int((g.N + BN - 1) / BN);
     const dim3 grid(g.tiles_m * g.tiles_n, split_count(g)), block(NT);
-    if (packed) hipLaunchKernelGGL((gemm_bf16_packed_kernel<BM, BN, BK, WM, WN, TERMS>), grid, block, 0, stream, g);
-    else if (!ta && !tb) hipLaunchKernelGGL((gemm_bf16_kernel<BM, BN, BK, WM, WN, false, false, TERMS>), grid, block, 0, stream, g);
+    if constexpr (TERMS != 3) {
+        if (packed) {
+            hipLaunchKernelGGL((gemm_bf16_packed_kernel<BM, BN, BK, WM, WN, TERMS>), grid, block, 0, stream, g);
+            return hipGetLastError();
+        }
+    } else if (packed) {
+        return hipErrorInvalidValue;   // no such plan: bf16x3 packs for its direct configurations only
+    }
+    if (!ta && !tb) hipLaunchKernelGGL((gemm_bf16_kernel<BM, BN, BK, WM, WN, false, false, TERMS>), grid, block, 0, stream, g);
     else if (!ta && tb) hipLaunchKernelGGL((gemm_bf16_kernel<BM, BN, BK, WM, WN, false, true, TERMS>), grid, block, 0, stream, g);
     else if (ta && !tb) hipLaunchKernelGGL((gemm_bf16_kernel<BM, BN, BK, WM, WN, true, false, TERMS>), grid, block, 0, stream, g);
     else hipLaunchKernelGGL((gemm_bf16_kernel<BM, BN, BK, WM, WN, true, true, TERMS>), grid, block, 0, stream, g);
@@ -268,10 +275,9 @@ hipError_t launch_gemm_bf16(int terms, int cfg, bool ta, bool tb, GemmArgs g, hi
 // Pre-pack of one operand for the BF16 paths: the logical R x Kd matrix
 // op(X) (stored R x Kd when T is false, Kd x R when true) is rounded (TERMS 1:
 // bf16, 16: fp16) or split into hi/lo (TERMS 3) once and written as
-// k-contiguous 16-bit rows
-// hi[Rp][ldq] (and lo[Rp][ldq]), zero outside R x Kd.  One workgroup of 256
-// threads per 128 x 128 tile; the tile goes through LDS so that both stored
-// layouts write whole 16-byte row chunks.
+// k-contiguous 16-bit rows of Kp (2 Kp) elements, zero outside R x Kd.  One
+// workgroup of 256 threads per 128 x 128 tile; the tile goes through LDS so
+// that both stored layouts write whole 16-byte row chunks.
 constexpr int PT = 128;          // pack tile
 constexpr int PROW = PT + 8;     // LDS row of the pack tile (bf16), T == false
 
@@ -282,24 +288,22 @@ constexpr int PROW = PT + 8;     // LDS row of the pack tile (bf16), T == false
 // eight to a bank).  Returns the element offset of element k of row r.
 MG_DEVICE int pt_swizzle(int r, int k) { return 8 * (((k >> 3) ^ (r >> 2)) & 15) + (k & 7); }
 
-// IL (bf16x3 only): one plane whose rows interleave the two terms per 32 k,
-// hi(k0 .. k0+31) then lo(k0 .. k0+31), so that a 32-deep panel of both
-// terms is one 128-byte row (row stride ldq = 2 Kp elements; `lo` unused).
-template <bool T, int TERMS, bool IL = false>
-__global__ __launch_bounds__(256) void bf16_pack_kernel(const float* __restrict__ X, int64_t ldx, int64_t R,
-                                                        int64_t Kd, int vec, uint16_t* __restrict__ hi,
-                                                        uint16_t* __restrict__ lo, int64_t ldq)
+// bf16x3: one plane whose rows interleave the two terms per 32 k, hi(k0 ..
+// k0+31) then lo(k0 .. k0+31), so that a 32-deep panel of both terms is one
+// 128-byte row (row stride 2 Kp elements).
+template <bool T, int TERMS>
+MG_DEVICE void bf16_pack_tile(const PackSrc& p, int64_t Kd, int64_t Kp, unsigned id, uint16_t* th, uint16_t* tl)
 {
-    static_assert(!IL || TERMS == 3, "interleaving needs two terms");
-    constexpr int ROW = T ? PT : PROW;
-    __shared__ __attribute__((aligned(16))) uint16_t th[PT * ROW];
-    __shared__ __attribute__((aligned(16))) uint16_t tl[TERMS == 3 ? PT * ROW : 8];
+    constexpr bool IL = TERMS == 3;
+    const float* __restrict__ X = static_cast<const float*>(p.X);
+    uint16_t* __restrict__ hi = static_cast<uint16_t*>(p.q);
+    const int64_t ldx = p.ldx, R = p.R, ldq = IL ? 2 * Kp : Kp;
     const int tid = threadIdx.x;
-    // blockIdx.x runs along the stored rows (over k tiles when T is false,
-    // over row tiles of op(X) when T is true), so that consecutive workgroups
-    // read neighbouring pieces of the same stored rows (measured: the other
-    // order makes either pack about 20 % slower)
-    const int64_t k0 = int64_t(T ? blockIdx.y : blockIdx.x) * PT, r0 = int64_t(T ? blockIdx.x : blockIdx.y) * PT;
+    // consecutive workgroups run along the stored rows (over k tiles when T is
+    // false, over row tiles of op(X) when T is true) and read neighbouring
+    // pieces of the same stored rows (measured: the other order makes either
+    // pack about 20 % slower)
+    const int64_t k0 = int64_t(T ? id / p.nx : id % p.nx) * PT, r0 = int64_t(T ? id % p.nx : id / p.nx) * PT;
     const int64_t sr0 = T ? k0 : r0, sc0 = T ? r0 : k0;      // stored tile origin
     const int64_t SRn = T ? Kd : R, SCn = T ? R : Kd;         // stored valid extent
     // 16 chunks of 4 floats per thread.  T == false: chunk s is stored row
@@ -310,7 +314,7 @@ __global__ __launch_bounds__(256) void bf16_pack_kernel(const float* __restrict_
     auto stored_row = [&](int s) { return T ? 4 * ((tid + 256 * (s >> 2)) / 32) + (s & 3) : (tid + 256 * s) / 32; };
     auto stored_col = [&](int s) { return T ? 4 * ((tid + 256 * (s >> 2)) % 32) : 4 * ((tid + 256 * s) % 32); };
     floatx4 v[16];
-    if (vec && sr0 + PT <= SRn && sc0 + PT <= SCn) {          // wave-uniform: interior tile
+    if (sr0 + PT <= SRn && sc0 + PT <= SCn && ldx < (int64_t(1) << 22)) {   // wave-uniform: interior tile
         const float* __restrict__ base = X + sr0 * ldx + sc0;
         const uint32_t ld32 = uint32_t(ldx);
 #pragma unroll
@@ -374,44 +378,44 @@ __global__ __launch_bounds__(256) void bf16_pack_kernel(const float* __restrict_
             *reinterpret_cast<uint4*>(dst + 32) = *reinterpret_cast<const uint4*>(&tl[off]);
         } else {
             *reinterpret_cast<uint4*>(hi + (r0 + r) * ldq + k0 + c) = *reinterpret_cast<const uint4*>(&th[off]);
-            if (TERMS == 3)
-                *reinterpret_cast<uint4*>(lo + (r0 + r) * ldq + k0 + c) = *reinterpret_cast<const uint4*>(&tl[off]);
         }
     }
 }
 
-hipError_t launch_bf16_pack(bool trans, int terms, const float* X, int64_t ldx, int64_t R, int64_t Kd,
-                            bool vec, uint16_t* hi, uint16_t* lo, int64_t ldq, int64_t Rp, int64_t Kp,
-                            hipStream_t stream)
+template <bool T0, bool T1, int TERMS>
+__global__ __launch_bounds__(256) void bf16_pack_kernel(PackArgs p)
 {
-    const dim3 grid(unsigned(trans ? Rp / PT : Kp / PT), unsigned(trans ? Kp / PT : Rp / PT)), block(256);
-    switch (terms) {
-    case 3:
-        if (trans) hipLaunchKernelGGL((bf16_pack_kernel<true, 3>), grid, block, 0, stream, X, ldx, R, Kd, int(vec), hi, lo, ldq);
-        else hipLaunchKernelGGL((bf16_pack_kernel<false, 3>), grid, block, 0, stream, X, ldx, R, Kd, int(vec), hi, lo, ldq);
-        break;
-    case 1:
-        if (trans) hipLaunchKernelGGL((bf16_pack_kernel<true, 1>), grid, block, 0, stream, X, ldx, R, Kd, int(vec), hi, lo, ldq);
-        else hipLaunchKernelGGL((bf16_pack_kernel<false, 1>), grid, block, 0, stream, X, ldx, R, Kd, int(vec), hi, lo, ldq);
-        break;
-    case 16:
-        if (trans) hipLaunchKernelGGL((bf16_pack_kernel<true, 16>), grid, block, 0, stream, X, ldx, R, Kd, int(vec), hi, lo, ldq);
-        else hipLaunchKernelGGL((bf16_pack_kernel<false, 16>), grid, block, 0, stream, X, ldx, R, Kd, int(vec), hi, lo, ldq);
-        break;
-    default: return hipErrorInvalidValue;
-    }
+    constexpr int ROW = T0 && T1 ? PT : PROW;
+    __shared__ __attribute__((aligned(16))) uint16_t th[PT * ROW];
+    __shared__ __attribute__((aligned(16))) uint16_t tl[TERMS == 3 ? PT * ROW : 8];
+    const bool second = blockIdx.x >= p.blocks0;
+    const unsigned id = second ? blockIdx.x - p.blocks0 : blockIdx.x;
+    if (T0 == T1) bf16_pack_tile<T0, TERMS>(p.src[second], p.Kd, p.Kp, id, th, tl);
+    else if (!second) bf16_pack_tile<T0, TERMS>(p.src[0], p.Kd, p.Kp, id, th, tl);
+    else bf16_pack_tile<T1, TERMS>(p.src[1], p.Kd, p.Kp, id, th, tl);
+}
+
+template <int TERMS>
+static hipError_t launch_pack_kind(const PackOperand* ops, int count, int64_t Kd, int64_t Kp, hipStream_t stream)
+{
+    PackArgs p{};
+    const dim3 grid(pack_args(ops, count, Kd, Kp, p)), block(256);
+    const bool t0 = ops[0].trans, t1 = ops[count - 1].trans;
+    if (t0 && t1) hipLaunchKernelGGL((bf16_pack_kernel<true, true, TERMS>), grid, block, 0, stream, p);
+    else if (t0) hipLaunchKernelGGL((bf16_pack_kernel<true, false, TERMS>), grid, block, 0, stream, p);
+    else if (t1) hipLaunchKernelGGL((bf16_pack_kernel<false, true, TERMS>), grid, block, 0, stream, p);
+    else hipLaunchKernelGGL((bf16_pack_kernel<false, false, TERMS>), grid, block, 0, stream, p);
     return hipGetLastError();
 }
 
-// bf16x3 pack into one plane per operand with the two terms interleaved per
-// 32 k (row stride ldq = 2 Kp elements).
-hipError_t launch_bf16_pack_interleaved(bool trans, const float* X, int64_t ldx, int64_t R, int64_t Kd, bool vec,
-                                        uint16_t* q, int64_t ldq, int64_t Rp, int64_t Kp, hipStream_t stream)
+hipError_t launch_bf16_pack(int kind, const PackOperand* ops, int count, int64_t Kd, int64_t Kp, hipStream_t stream)
 {
-    const dim3 grid(unsigned(trans ? Rp / PT : Kp / PT), unsigned(trans ? Kp / PT : Rp / PT)), block(256);
-    if (trans) hipLaunchKernelGGL((bf16_pack_kernel<true, 3, true>), grid, block, 0, stream, X, ldx, R, Kd, int(vec), q, nullptr, ldq);
-    else hipLaunchKernelGGL((bf16_pack_kernel<false, 3, true>), grid, block, 0, stream, X, ldx, R, Kd, int(vec), q, nullptr, ldq);
-    return hipGetLastError();
+    switch (kind) {
+    case 1: return launch_pack_kind<1>(ops, count, Kd, Kp, stream);
+    case 3: return launch_pack_kind<3>(ops, count, Kd, Kp, stream);
+    case 16: return launch_pack_kind<16>(ops, count, Kd, Kp, stream);
+    default: return hipErrorInvalidValue;
+    }
 }
 
 // ---------------------------------------------------------------------------

@@ -68,22 +68,21 @@ MG_DEVICE int scale_byte(float amax)
 // most two to a bank (unswizzled, the writes meet eight to a bank).
 MG_DEVICE int qt_swizzle(int r, int k) { return 16 * (((k >> 4) ^ ((r >> 2) + (r >> 5))) & 7) + (k & 15); }
 
-// One workgroup of 256 threads per 128 x 128 tile of the logical R x Kd matrix
-// op(X).  T == false: X stored R x Kd (k contiguous); T == true: stored Kd x R.
+// One workgroup of 256 threads packs tile `id` (128 x 128) of the logical R x
+// Kd matrix op(X).  T == false: X stored R x Kd (k contiguous); T == true:
+// stored Kd x R.
 template <bool T>
-__global__ __launch_bounds__(256) void fp8_pack_kernel(const float* __restrict__ X, int64_t ldx,
-                                                       int64_t R, int64_t Kd,
-                                                       uint8_t* __restrict__ q, int64_t ldq,
-                                                       uint8_t* __restrict__ sc, int64_t lds)
+MG_DEVICE void fp8_pack_tile(const PackSrc& p, int64_t Kd, int64_t Kp, unsigned id, uint8_t* tile, float* wmax)
 {
-    __shared__ __attribute__((aligned(16))) uint8_t tile[QT * QROW];
-    __shared__ float wmax[4];
+    const float* __restrict__ X = static_cast<const float*>(p.X);
+    uint8_t* __restrict__ q = static_cast<uint8_t*>(p.q);
+    const int64_t ldx = p.ldx, R = p.R, ldq = Kp;
     const int tid = threadIdx.x;
-    // blockIdx.x runs along the stored rows (over k tiles when T is false,
-    // over row tiles of op(X) when T is true), so that consecutive workgroups
-    // read neighbouring pieces of the same stored rows (measured: the other
-    // order makes either pack about 20 % slower)
-    const int kt = T ? blockIdx.y : blockIdx.x, rt = T ? blockIdx.x : blockIdx.y;
+    // consecutive workgroups run along the stored rows (over k tiles when T is
+    // false, over row tiles of op(X) when T is true) and read neighbouring
+    // pieces of the same stored rows (measured: the other order makes either
+    // pack about 20 % slower)
+    const int kt = T ? id / p.nx : id % p.nx, rt = T ? id % p.nx : id / p.nx;
     const int64_t k0 = int64_t(kt) * QT;
     const int64_t r0 = int64_t(rt) * QT;
 
@@ -99,10 +98,11 @@ __global__ __launch_bounds__(256) void fp8_pack_kernel(const float* __restrict__
     // stored tile origin and valid extent
     const int64_t sr0 = T ? k0 : r0, sc0 = T ? r0 : k0;
     const int64_t SRn = T ? Kd : R, SCn = T ? R : Kd;
-    if (sr0 + QT <= SRn && sc0 + QT <= SCn) {   // wave-uniform: interior tile
+    if (sr0 + QT <= SRn && sc0 + QT <= SCn && ldx < (int64_t(1) << 22)) {   // wave-uniform: interior tile
         const float* __restrict__ base = X + sr0 * ldx + sc0;
+        const uint32_t ld32 = uint32_t(ldx);
 #pragma unroll
-        for (int s = 0; s < 16; ++s) v[s] = *reinterpret_cast<const floatx4u*>(base + stored_row(s) * ldx + stored_col(s));
+        for (int s = 0; s < 16; ++s) v[s] = load16(base, (uint32_t(stored_row(s)) * ld32 + uint32_t(stored_col(s))) * 4u);
     } else if (R == 0 || Kd == 0) {
 #pragma unroll
         for (int s = 0; s < 16; ++s) v[s] = floatx4{0.f, 0.f, 0.f, 0.f};
@@ -163,16 +163,30 @@ __global__ __launch_bounds__(256) void fp8_pack_kernel(const float* __restrict__
         const int lc = T ? qt_swizzle(r, c) : c;
         *reinterpret_cast<uint4*>(q + (r0 + r) * ldq + k0 + c) = *reinterpret_cast<const uint4*>(&tile[r * QROW + lc]);
     }
-    if (tid == 0) sc[rt * lds + kt] = uint8_t(sbyte);
+    if (tid == 0) p.scales[int64_t(rt) * (Kp / QT) + kt] = uint8_t(sbyte);
 }
 
-hipError_t launch_fp8_pack(bool trans, const float* X, int64_t ldx, int64_t R, int64_t Kd, uint8_t* q,
-                           int64_t ldq, uint8_t* sc, int64_t lds, int64_t Rp, int64_t Kp,
-                           hipStream_t stream)
+template <bool T0, bool T1>
+__global__ __launch_bounds__(256) void fp8_pack_kernel(PackArgs p)
 {
-    const dim3 grid(unsigned(trans ? Rp / QT : Kp / QT), unsigned(trans ? Kp / QT : Rp / QT)), block(256);
-    if (trans) hipLaunchKernelGGL(fp8_pack_kernel<true>, grid, block, 0, stream, X, ldx, R, Kd, q, ldq, sc, lds);
-    else hipLaunchKernelGGL(fp8_pack_kernel<false>, grid, block, 0, stream, X, ldx, R, Kd, q, ldq, sc, lds);
+    __shared__ __attribute__((aligned(16))) uint8_t tile[QT * QROW];
+    __shared__ float wmax[4];
+    const bool second = blockIdx.x >= p.blocks0;
+    const unsigned id = second ? blockIdx.x - p.blocks0 : blockIdx.x;
+    if (T0 == T1) fp8_pack_tile<T0>(p.src[second], p.Kd, p.Kp, id, tile, wmax);
+    else if (!second) fp8_pack_tile<T0>(p.src[0], p.Kd, p.Kp, id, tile, wmax);
+    else fp8_pack_tile<T1>(p.src[1], p.Kd, p.Kp, id, tile, wmax);
+}
+
+hipError_t launch_fp8_pack(const PackOperand* ops, int count, int64_t Kd, int64_t Kp, hipStream_t stream)
+{
+    PackArgs p{};
+    const dim3 grid(pack_args(ops, count, Kd, Kp, p)), block(256);
+    const bool t0 = ops[0].trans, t1 = ops[count - 1].trans;
+    if (t0 && t1) hipLaunchKernelGGL((fp8_pack_kernel<true, true>), grid, block, 0, stream, p);
+    else if (t0) hipLaunchKernelGGL((fp8_pack_kernel<true, false>), grid, block, 0, stream, p);
+    else if (t1) hipLaunchKernelGGL((fp8_pack_kernel<false, true>), grid, block, 0, stream, p);
+    else hipLaunchKernelGGL((fp8_pack_kernel<false, false>), grid, block, 0, stream, p);
     return hipGetLastError();
 }
 

@@ -41,22 +41,23 @@ constexpr int IROW = IT + 16;    // LDS row of the pack tile (bytes), T == false
 // writes meet eight to a bank).  Returns the byte offset of byte k of row r.
 MG_DEVICE int it_swizzle(int r, int k) { return 16 * (((k >> 4) ^ (r >> 4)) & 7) + (k & 15); }
 
-// One workgroup of 256 threads per 128 x 128 tile of the logical R x Kd
-// matrix op(X).  T == false: X stored R x Kd (k contiguous); T == true:
+// One workgroup of 256 threads packs tile `id` (128 x 128) of the logical R x
+// Kd matrix op(X).  T == false: X stored R x Kd (k contiguous); T == true:
 // stored Kd x R.  16-byte loads at any address (an odd row stride or base
 // costs the lines that a load straddles).
 template <bool T>
-__global__ __launch_bounds__(256) void i8_pack_kernel(const int8_t* __restrict__ X, int64_t ldx, int64_t R,
-                                                      int64_t Kd, int8_t* __restrict__ q, int64_t ldq)
+MG_DEVICE void i8_pack_tile(const PackSrc& p, int64_t Kd, int64_t Kp, unsigned id, uint8_t* tile)
 {
+    const int8_t* __restrict__ X = static_cast<const int8_t*>(p.X);
+    int8_t* __restrict__ q = static_cast<int8_t*>(p.q);
+    const int64_t ldx = p.ldx, R = p.R, ldq = Kp;
     constexpr int ROW = T ? IT : IROW;
-    __shared__ __attribute__((aligned(16))) uint8_t tile[IT * ROW];
     const int tid = threadIdx.x;
-    // blockIdx.x runs along the stored rows (over k tiles when T is false,
-    // over row tiles of op(X) when T is true), so that consecutive workgroups
-    // read neighbouring pieces of the same stored rows (measured: the other
-    // order makes either pack about 20 % slower)
-    const int64_t k0 = int64_t(T ? blockIdx.y : blockIdx.x) * IT, r0 = int64_t(T ? blockIdx.x : blockIdx.y) * IT;
+    // consecutive workgroups run along the stored rows (over k tiles when T is
+    // false, over row tiles of op(X) when T is true) and read neighbouring
+    // pieces of the same stored rows (measured: the other order makes either
+    // pack about 20 % slower)
+    const int64_t k0 = int64_t(T ? id / p.nx : id % p.nx) * IT, r0 = int64_t(T ? id % p.nx : id / p.nx) * IT;
     const int64_t sr0 = T ? k0 : r0, sc0 = T ? r0 : k0;      // stored tile origin
     const int64_t SRn = T ? Kd : R, SCn = T ? R : Kd;         // stored valid extent
 
@@ -109,12 +110,26 @@ __global__ __launch_bounds__(256) void i8_pack_kernel(const int8_t* __restrict__
     }
 }
 
-hipError_t launch_i8_pack(bool trans, const int8_t* X, int64_t ldx, int64_t R, int64_t Kd, int8_t* q, int64_t ldq,
-                          int64_t Rp, int64_t Kp, hipStream_t stream)
+template <bool T0, bool T1>
+__global__ __launch_bounds__(256) void i8_pack_kernel(PackArgs p)
 {
-    const dim3 grid(unsigned(trans ? Rp / IT : Kp / IT), unsigned(trans ? Kp / IT : Rp / IT)), block(256);
-    if (trans) hipLaunchKernelGGL(i8_pack_kernel<true>, grid, block, 0, stream, X, ldx, R, Kd, q, ldq);
-    else hipLaunchKernelGGL(i8_pack_kernel<false>, grid, block, 0, stream, X, ldx, R, Kd, q, ldq);
+    __shared__ __attribute__((aligned(16))) uint8_t tile[IT * IROW];
+    const bool second = blockIdx.x >= p.blocks0;
+    const unsigned id = second ? blockIdx.x - p.blocks0 : blockIdx.x;
+    if (T0 == T1) i8_pack_tile<T0>(p.src[second], p.Kd, p.Kp, id, tile);
+    else if (!second) i8_pack_tile<T0>(p.src[0], p.Kd, p.Kp, id, tile);
+    else i8_pack_tile<T1>(p.src[1], p.Kd, p.Kp, id, tile);
+}
+
+hipError_t launch_i8_pack(const PackOperand* ops, int count, int64_t Kd, int64_t Kp, hipStream_t stream)
+{
+    PackArgs p{};
+    const dim3 grid(pack_args(ops, count, Kd, Kp, p)), block(256);
+    const bool t0 = ops[0].trans, t1 = ops[count - 1].trans;
+    if (t0 && t1) hipLaunchKernelGGL((i8_pack_kernel<true, true>), grid, block, 0, stream, p);
+    else if (t0) hipLaunchKernelGGL((i8_pack_kernel<true, false>), grid, block, 0, stream, p);
+    else if (t1) hipLaunchKernelGGL((i8_pack_kernel<false, true>), grid, block, 0, stream, p);
+    else hipLaunchKernelGGL((i8_pack_kernel<false, false>), grid, block, 0, stream, p);
     return hipGetLastError();
 }
 

@@ -21,28 +21,66 @@ extern const int kNumSgemmConfigs;
 hipError_t launch_sgemm(int cfg, bool ta, bool tb, GemmArgs g, hipStream_t stream);
 hipError_t launch_sgemm_direct(int cfg, bool ta, bool tb, GemmArgs g, hipStream_t stream);
 hipError_t launch_sgemm_valu(int cfg, bool ta, bool tb, GemmArgs g, hipStream_t stream);
+
+// ---- Pack of one or two operands in one launch (a GEMM's two packs are
+// independent: together they pay one launch and one tail).
+// One logical R x Kd operand, stored R x Kd, or Kd x R when trans (row stride
+// ldx), packed into q as Rp (a multiple of 128) rows.
+struct PackOperand {
+    bool trans;
+    const void* X;
+    int64_t ldx, R;
+    void* q;
+    uint8_t* scales;   // FP8 only
+    int64_t Rp;
+};
+
+// The same for the kernels: one workgroup per 128 x 128 tile, numbered along
+// the stored rows (nx of them to a row of tiles).
+struct PackSrc {
+    const void* X;
+    int64_t ldx, R;
+    void* q;
+    uint8_t* scales;
+    unsigned nx;
+};
+struct PackArgs {
+    PackSrc src[2];
+    unsigned blocks0;   // workgroups of src[0]; the others pack src[1]
+    int64_t Kd, Kp;
+};
+
+// Fills the kernels' arguments; returns the number of workgroups.
+inline unsigned pack_args(const PackOperand* ops, int count, int64_t Kd, int64_t Kp, PackArgs& p)
+{
+    unsigned total = 0;
+    for (int i = 0; i < count; ++i) {
+        const PackOperand& o = ops[i];
+        p.src[i] = {o.X, o.ldx, o.R, o.q, o.scales, unsigned((o.trans ? o.Rp : Kp) / 128)};
+        total += unsigned((o.Rp / 128) * (Kp / 128));
+        if (i == 0) p.blocks0 = total;
+    }
+    p.Kd = Kd;
+    p.Kp = Kp;
+    return total;
+}
+
 extern const SgemmConfig kBf16Configs[];
 extern const int kNumBf16Configs;
 
 // terms == 1: plain BF16; terms == 3: bf16x3 split.  packed: g.A / g.B are
-// the hi planes written by launch_bf16_pack (plane_a / plane_b to the lo
-// planes), or, for bf16x3 with configuration 6, the interleaved planes
-// written by launch_bf16_pack_interleaved (row stride lda / ldb = 2 Kp).
+// the planes written by launch_bf16_pack.
 hipError_t launch_gemm_bf16(int terms, int cfg, bool ta, bool tb, GemmArgs g, hipStream_t stream,
                             bool packed = false);
-hipError_t launch_bf16_pack(bool trans, int terms, const float* X, int64_t ldx, int64_t R, int64_t Kd,
-                            bool vec, uint16_t* hi, uint16_t* lo, int64_t ldq, int64_t Rp, int64_t Kp,
-                            hipStream_t stream);
-hipError_t launch_bf16_pack_interleaved(bool trans, const float* X, int64_t ldx, int64_t R, int64_t Kd, bool vec,
-                                        uint16_t* q, int64_t ldq, int64_t Rp, int64_t Kp, hipStream_t stream);
+// kind 1: bf16, 16: binary16 rows of Kp elements; 3: bf16x3's two terms
+// interleaved, rows of 2 Kp.
+hipError_t launch_bf16_pack(int kind, const PackOperand* ops, int count, int64_t Kd, int64_t Kp, hipStream_t stream);
 hipError_t launch_bf16_split(const float* x, int64_t n, uint16_t* hi, uint16_t* lo, hipStream_t stream);
 
 extern const SgemmConfig kFp8Configs[];
 extern const int kNumFp8Configs;
 
-hipError_t launch_fp8_pack(bool trans, const float* X, int64_t ldx, int64_t R, int64_t Kd, uint8_t* q,
-                           int64_t ldq, uint8_t* sc, int64_t lds, int64_t Rp, int64_t Kp,
-                           hipStream_t stream);
+hipError_t launch_fp8_pack(const PackOperand* ops, int count, int64_t Kd, int64_t Kp, hipStream_t stream);
 hipError_t launch_gemm_fp8(int cfg, Fp8Args g, hipStream_t stream);
 
 // One problem of a batched launch, as the persistent kernel reads it.
@@ -97,8 +135,7 @@ struct I8Args {
 };
 extern const SgemmConfig kI8Configs[];
 extern const int kNumI8Configs;
-hipError_t launch_i8_pack(bool trans, const int8_t* X, int64_t ldx, int64_t R, int64_t Kd, int8_t* q, int64_t ldq,
-                          int64_t Rp, int64_t Kp, hipStream_t stream);
+hipError_t launch_i8_pack(const PackOperand* ops, int count, int64_t Kd, int64_t Kp, hipStream_t stream);
 hipError_t launch_gemm_i8(int cfg, I8Args g, hipStream_t stream);
 hipError_t launch_scale_c_i32(int32_t* C, int64_t M, int64_t N, int64_t ldc, int32_t beta, hipStream_t stream);
 

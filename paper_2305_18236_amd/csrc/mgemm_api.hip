@@ -754,22 +754,19 @@ bool uses_planes(int path, int cfg, int64_t M, int64_t N, int64_t K)
 
 struct Bf16Workspace {
     int64_t Mp, Np, Kp;
-    size_t a_hi, a_lo, b_hi, b_lo, total;
+    size_t a, b, total;
 };
 
 Bf16Workspace bf16_workspace(int path, int64_t M, int64_t N, int64_t K)
 {
     Bf16Workspace w{};
-    const int nl = path == MG_PATH_BF16X3 ? 2 : 1;
+    const int nl = path == MG_PATH_BF16X3 ? 2 : 1;   // terms, interleaved in one plane
     w.Mp = round_up(M, 256);
     w.Np = round_up(N, 256);
     w.Kp = round_up(K, 128);
-    const size_t pa = align256(size_t(w.Mp) * size_t(w.Kp) * 2), pb = align256(size_t(w.Np) * size_t(w.Kp) * 2);
-    w.a_hi = 0;
-    w.a_lo = pa;                       // used only when nl == 2
-    w.b_hi = size_t(nl) * pa;
-    w.b_lo = w.b_hi + pb;
-    w.total = size_t(nl) * (pa + pb);
+    w.a = 0;
+    w.b = nl * align256(size_t(w.Mp) * size_t(w.Kp) * 2);
+    w.total = w.b + nl * align256(size_t(w.Np) * size_t(w.Kp) * 2);
     return w;
 }
 
@@ -829,9 +826,15 @@ I8Workspace i8_workspace(int64_t M, int64_t N, int64_t K)
     return w;
 }
 
-int run_i8_pack(bool trans, int64_t R, int64_t K, const int8_t* X, int64_t ldx, int8_t* q, hipStream_t stream)
+// Pack of one operand op(X), R x K, or (ops[1]) of both of a GEMM's.
+mg::PackOperand pack_operand(bool trans, int64_t R, const void* X, int64_t ldx, void* q, uint8_t* sc = nullptr)
 {
-    return hip_status(mg::launch_i8_pack(trans, X, ldx, R, K, q, fp8_kp(K), fp8_rows(R), fp8_kp(K), stream));
+    return {trans, X, ldx, R, q, sc, fp8_rows(R)};
+}
+
+int run_i8_pack(const mg::PackOperand* ops, int count, int64_t K, hipStream_t stream)
+{
+    return hip_status(mg::launch_i8_pack(ops, count, K, fp8_kp(K), stream));
 }
 
 int run_i8_packed(int64_t M, int64_t N, int64_t K, int32_t alpha, const int8_t* qA, const int8_t* qB, int32_t beta,
@@ -865,11 +868,9 @@ int run_fp8_packed(int64_t M, int64_t N, int64_t K, float alpha, const uint8_t* 
     return hip_status(mg::launch_gemm_fp8(cfg, g, stream));
 }
 
-int run_fp8_pack(bool trans, int64_t R, int64_t K, const float* X, int64_t ldx, uint8_t* q,
-                 uint8_t* sc, hipStream_t stream)
+int run_fp8_pack(const mg::PackOperand* ops, int count, int64_t K, hipStream_t stream)
 {
-    const int64_t Rp = fp8_rows(R), Kp = fp8_kp(K);
-    return hip_status(mg::launch_fp8_pack(trans, X, ldx, R, K, q, Kp, sc, Kp / 128, Rp, Kp, stream));
+    return hip_status(mg::launch_fp8_pack(ops, count, K, fp8_kp(K), stream));
 }
 
 // forced > tuned for this exact shape > tuned for its bucket > default
@@ -960,36 +961,14 @@ int run_gemm(int path, bool ta, bool tb, int64_t M, int64_t N, int64_t K, float 
         // pack each operand once, then multiply the packed planes
         const Bf16Workspace w = bf16_workspace(path, M, N, K);
         uint8_t* base = static_cast<uint8_t*>(bf16_planes);
-        uint16_t* ahi = reinterpret_cast<uint16_t*>(base + w.a_hi);
-        uint16_t* alo = reinterpret_cast<uint16_t*>(base + w.a_lo);
-        uint16_t* bhi = reinterpret_cast<uint16_t*>(base + w.b_hi);
-        uint16_t* blo = reinterpret_cast<uint16_t*>(base + w.b_lo);
-        if (terms == 3) {
-            // interleaved planes (configuration 6): A at a_hi, B at b_hi,
-            // 2 Kp elements per row, both terms in one plane
-            hipError_t e = mg::launch_bf16_pack_interleaved(ta, A, lda, M, K, va, ahi, 2 * w.Kp,
-                                                            w.Mp, w.Kp, stream);
-            if (e != hipSuccess) return hip_status(e);
-            e = mg::launch_bf16_pack_interleaved(!tb, B, ldb, N, K, vb, bhi, 2 * w.Kp, w.Np, w.Kp,
-                                                 stream);
-            if (e != hipSuccess) return hip_status(e);
-            g.A = reinterpret_cast<const float*>(ahi);
-            g.B = reinterpret_cast<const float*>(bhi);
-            g.lda = g.ldb = 2 * w.Kp;
-            return finish(mg::launch_gemm_bf16(terms, cfg, false, true, g, stream, true));
-        }
-        hipError_t e = mg::launch_bf16_pack(ta, terms, A, lda, M, K, va, ahi, alo, w.Kp,
-                                            w.Mp, w.Kp, stream);
-        if (e != hipSuccess) return hip_status(e);
         // op(B)^T is N x K: stored as is when transB is 'T', transposed when 'N'
-        e = mg::launch_bf16_pack(!tb, terms, B, ldb, N, K, vb, bhi, blo, w.Kp, w.Np, w.Kp,
-                                 stream);
+        const mg::PackOperand ops[2] = {{ta, A, lda, M, base + w.a, nullptr, w.Mp},
+                                        {!tb, B, ldb, N, base + w.b, nullptr, w.Np}};
+        const hipError_t e = mg::launch_bf16_pack(terms, ops, 2, K, w.Kp, stream);
         if (e != hipSuccess) return hip_status(e);
-        g.A = reinterpret_cast<const float*>(ahi);
-        g.B = reinterpret_cast<const float*>(bhi);
-        g.lda = g.ldb = w.Kp;
-        g.plane_a = int64_t(w.a_lo - w.a_hi) / 2;
-        g.plane_b = int64_t(w.b_lo - w.b_hi) / 2;
+        g.A = reinterpret_cast<const float*>(base + w.a);
+        g.B = reinterpret_cast<const float*>(base + w.b);
+        g.lda = g.ldb = terms == 3 ? 2 * w.Kp : w.Kp;   // both terms in one plane
         return finish(mg::launch_gemm_bf16(terms, cfg, false, true, g, stream, true));
     }
     default: return MG_ERR_UNSUPPORTED;
@@ -1174,10 +1153,10 @@ int mg_gemm(int path, char transA, char transB, int64_t M, int64_t N, int64_t K,
     if (path == MG_PATH_FP8_T128) {
         const Fp8Workspace w = fp8_workspace(M, N, K);
         uint8_t* base = static_cast<uint8_t*>(workspace);
-        st = run_fp8_pack(is_t(transA), M, K, A, lda, base + w.qa, base + w.sa, s);
-        if (st != MG_OK) return st;
         // op(B)^T is N x K: stored as is when transB is 'T', transposed when 'N'.
-        st = run_fp8_pack(!is_t(transB), N, K, B, ldb, base + w.qb, base + w.sb, s);
+        const mg::PackOperand ops[2] = {pack_operand(is_t(transA), M, A, lda, base + w.qa, base + w.sa),
+                                        pack_operand(!is_t(transB), N, B, ldb, base + w.qb, base + w.sb)};
+        st = run_fp8_pack(ops, 2, K, s);
         if (st != MG_OK) return st;
         return run_fp8_packed(M, N, K, alpha, base + w.qa, base + w.sa, base + w.qb, base + w.sb,
                               beta, C, ldc, s);
@@ -1276,7 +1255,8 @@ int mg_fp8_pack(char trans, int64_t R, int64_t K, const float* X, int64_t ldx, u
     if (q == nullptr) return -6;
     if (scales == nullptr) return -7;
     if (R > INT_MAX || K > INT_MAX) return MG_ERR_TOO_LARGE;
-    return run_fp8_pack(is_t(trans), R, K, X, ldx, q, scales, reinterpret_cast<hipStream_t>(stream));
+    const mg::PackOperand op = pack_operand(is_t(trans), R, X, ldx, q, scales);
+    return run_fp8_pack(&op, 1, K, reinterpret_cast<hipStream_t>(stream));
 }
 
 int mg_gemm_fp8_packed(int64_t M, int64_t N, int64_t K, float alpha, const uint8_t* qA,
@@ -1399,10 +1379,10 @@ int mg_gemm_i8(char transA, char transB, int64_t M, int64_t N, int64_t K, int32_
     }
     const I8Workspace w = i8_workspace(M, N, K);
     int8_t* base = static_cast<int8_t*>(workspace);
-    st = run_i8_pack(is_t(transA), M, K, A, lda, base + w.qa, s);
-    if (st != MG_OK) return st;
     // op(B)^T is N x K: stored as is when transB is 'T', transposed when 'N'.
-    st = run_i8_pack(!is_t(transB), N, K, B, ldb, base + w.qb, s);
+    const mg::PackOperand ops[2] = {pack_operand(is_t(transA), M, A, lda, base + w.qa),
+                                    pack_operand(!is_t(transB), N, B, ldb, base + w.qb)};
+    st = run_i8_pack(ops, 2, K, s);
     if (st != MG_OK) return st;
     return run_i8_packed(M, N, K, alpha, base + w.qa, base + w.qb, beta, C, ldc, s);
 }
@@ -1426,7 +1406,8 @@ int mg_i8_pack(char trans, int64_t R, int64_t K, const int8_t* X, int64_t ldx, i
     if (ldx < (cols > 1 ? cols : 1) || !fits(rows, ldx)) return -5;
     if (q == nullptr || (reinterpret_cast<uintptr_t>(q) & 15) != 0) return -6;
     if (R > INT_MAX || K > kMaxI8K) return MG_ERR_TOO_LARGE;
-    return run_i8_pack(is_t(trans), R, K, X, ldx, q, reinterpret_cast<hipStream_t>(stream));
+    const mg::PackOperand op = pack_operand(is_t(trans), R, X, ldx, q);
+    return run_i8_pack(&op, 1, K, reinterpret_cast<hipStream_t>(stream));
 }
 
 int mg_gemm_i8_packed(int64_t M, int64_t N, int64_t K, int32_t alpha, const int8_t* qA, const int8_t* qB,

@@ -224,54 +224,50 @@ constexpr int bf16_lds_elems() { return 2 * (TERMS == 3 ? 2 : 1) * (BM + BN) * (
 // One BM x BN output tile (tm, tn), computed by the whole workgroup.  smem:
 // bf16_lds_elems() 16-bit elements of LDS, 16-byte aligned.  Ends with a
 // workgroup barrier after the last LDS read.
-// One operand panel read from PRE-PACKED bf16 planes (bf16_pack_kernel): rows
-// of ld bf16 (k-contiguous, zero-padded), hi plane at `hi`, lo plane at
-// hi + plane.  The pack to LDS is a plain 16-byte copy; lanes take four
-// 16-byte chunks of one row, rows in row_perm order, so a 16-lane write
-// covers rows 0, 4, 8, 12 at bank offsets 0, 16, 32, 48 (conflict-free).
-template <int ROWS, int BK, int LDR, int NT, int TERMS>
+// One operand panel read from a PRE-PACKED 16-bit plane (bf16_pack_kernel):
+// rows of ld elements (k-contiguous, zero-padded).  The pack to LDS is a plain
+// 16-byte copy; lanes take four 16-byte chunks of one row, rows in row_perm
+// order, so a 16-lane write covers rows 0, 4, 8, 12 at bank offsets 0, 16, 32,
+// 48 (conflict-free).  (Single-term kinds: bf16x3's planes go to the direct
+// kernel.)
+template <int ROWS, int BK, int LDR, int NT>
 struct BfPackedPanel {
-    static constexpr int CPR = BK / 8;          // 16-byte chunks per row and plane
+    static constexpr int CPR = BK / 8;          // 16-byte chunks per row
     static constexpr int CHUNKS = ROWS * CPR;
     static constexpr int PER = (CHUNKS + NT - 1) / NT;
-    static constexpr int NL = (TERMS == 3) ? 2 : 1;
     static_assert(ROWS % 16 == 0, "row permutation works on groups of 16 rows");
-    uint4 v[NL][PER];
+    uint4 v[PER];
 
     struct Offsets {};
     MG_DEVICE static Offsets offsets(int64_t, int64_t, int64_t, int) { return {}; }
 
-    MG_DEVICE void load(const uint16_t* __restrict__ hi, int64_t plane, int64_t ld, int64_t mn0,
-                        int64_t k0, int tid)
+    MG_DEVICE void load(const uint16_t* __restrict__ q, int64_t ld, int64_t mn0, int64_t k0, int tid)
     {
-        const uint16_t* __restrict__ base = hi + mn0 * ld + k0;
+        const uint16_t* __restrict__ base = q + mn0 * ld + k0;
         const uint32_t ld32 = uint32_t(ld);
 #pragma unroll
         for (int s = 0; s < PER; ++s) {
             const int q = tid + s * NT;
             if (CHUNKS % NT != 0 && q >= CHUNKS) break;
             const uint32_t r = row_perm(q / CPR), c = (q % CPR) * 8;
-            const uint32_t off = (r * ld32 + c) * 2u;
-            v[0][s] = load16u(base, off);
-            if (TERMS == 3) v[NL - 1][s] = load16u(base + plane, off);
+            v[s] = load16u(base, (r * ld32 + c) * 2u);
         }
     }
 
-    MG_DEVICE void store(uint16_t* hi_lds, uint16_t* lo_lds, int tid) const
+    MG_DEVICE void store(uint16_t* lds, uint16_t*, int tid) const
     {
 #pragma unroll
-        for (int s = 0; s < PER; ++s) store_chunk(hi_lds, lo_lds, tid, s);
+        for (int s = 0; s < PER; ++s) store_chunk(lds, tid, s);
     }
 
     // One of the PER chunks, so that a caller can spread a panel's LDS writes
     // between its matrix instructions.
-    MG_DEVICE void store_chunk(uint16_t* hi_lds, uint16_t* lo_lds, int tid, int s) const
+    MG_DEVICE void store_chunk(uint16_t* lds, int tid, int s) const
     {
         const int q = tid + s * NT;
         if (CHUNKS % NT != 0 && q >= CHUNKS) return;
         const int r = row_perm(q / CPR), c = (q % CPR) * 8;
-        *reinterpret_cast<uint4*>(hi_lds + r * LDR + c) = v[0][s];
-        if (TERMS == 3) *reinterpret_cast<uint4*>(lo_lds + r * LDR + c) = v[NL - 1][s];
+        *reinterpret_cast<uint4*>(lds + r * LDR + c) = v[s];
     }
 };
 
@@ -281,11 +277,11 @@ struct BfLoaderSel {
 };
 template <int ROWS, int BK, int LDR, int NT, bool KSRC, int TERMS>
 struct BfLoaderSel<true, ROWS, BK, LDR, NT, KSRC, TERMS> {
-    using type = BfPackedPanel<ROWS, BK, LDR, NT, TERMS>;
+    using type = BfPackedPanel<ROWS, BK, LDR, NT>;
 };
 
-// PACKED: g.A / g.B point at the hi planes of pre-packed op(A) / op(B)^T
-// (bf16, row stride lda / ldb, zero-padded to whole tiles and panels), TA/TB
+// PACKED: g.A / g.B point at the planes of pre-packed op(A) / op(B)^T
+// (16-bit, row stride lda / ldb, zero-padded to whole tiles and panels), TA/TB
 // are ignored and no bounds checks are needed on the loads.
 template <int BM, int BN, int BK, int WM, int WN, bool TA, bool TB, int TERMS, bool PACKED = false>
 MG_DEVICE void bf16_tile(const GemmArgs& g, int tm, int tn, uint16_t* smem)
@@ -316,8 +312,8 @@ MG_DEVICE void bf16_tile(const GemmArgs& g, int tm, int tn, uint16_t* smem)
 
     auto fetch = [&](int64_t k0) {
         if constexpr (PACKED) {
-            pa.load(reinterpret_cast<const uint16_t*>(g.A), g.plane_a, g.lda, m0, k0, tid);
-            pb.load(reinterpret_cast<const uint16_t*>(g.B), g.plane_b, g.ldb, n0, k0, tid);
+            pa.load(reinterpret_cast<const uint16_t*>(g.A), g.lda, m0, k0, tid);
+            pb.load(reinterpret_cast<const uint16_t*>(g.B), g.ldb, n0, k0, tid);
         } else {
             pa.load(g.A, g.lda, m0, k0, g.M, g.K, g.vec_a, oa, tid);
             pb.load(g.B, g.ldb, n0, k0, g.N, g.K, g.vec_b, ob, tid);
@@ -415,7 +411,8 @@ MG_DEVICE void bf16_tile(const GemmArgs& g, int tm, int tn, uint16_t* smem)
         }
     };
 
-    if constexpr (PACKED && TERMS != 3 && WM * WN < 128 * 128) {
+    static_assert(!PACKED || TERMS != 3, "bf16x3's planes go to the direct kernel");
+    if constexpr (PACKED && WM * WN < 128 * 128) {
         // Pre-packed single-term operands: two register staging sets, so the
         // panel packed during panel kt (panel kt+1) was fetched a whole panel
         // earlier and its LDS writes are spread between panel kt's matrix
@@ -429,8 +426,8 @@ MG_DEVICE void bf16_tile(const GemmArgs& g, int tm, int tn, uint16_t* smem)
         const uint16_t* qa = reinterpret_cast<const uint16_t*>(g.A);
         const uint16_t* qb = reinterpret_cast<const uint16_t*>(g.B);
         auto load = [&](PA& xa, PB& xb, int kp) {
-            xa.load(qa, g.plane_a, g.lda, m0, int64_t(kp) * BK, tid);
-            xb.load(qb, g.plane_b, g.ldb, n0, int64_t(kp) * BK, tid);
+            xa.load(qa, g.lda, m0, int64_t(kp) * BK, tid);
+            xb.load(qb, g.ldb, n0, int64_t(kp) * BK, tid);
         };
         if (nk > 0) {
             load(pa0, pb0, 0);
@@ -444,9 +441,9 @@ MG_DEVICE void bf16_tile(const GemmArgs& g, int tm, int tn, uint16_t* smem)
             load(pa0, pb0, kt + 2 < nk ? kt + 2 : nk - 1);
             panel(0, [&](int s) {
 #pragma unroll
-                for (int q = s; q < PA::PER; q += STEPS) pa1.store_chunk(As[1][0], As[1][NL - 1], tid, q);
+                for (int q = s; q < PA::PER; q += STEPS) pa1.store_chunk(As[1][0], tid, q);
 #pragma unroll
-                for (int q = s; q < PB::PER; q += STEPS) pb1.store_chunk(Bs[1][0], Bs[1][NL - 1], tid, q);
+                for (int q = s; q < PB::PER; q += STEPS) pb1.store_chunk(Bs[1][0], tid, q);
             });
             __syncthreads();
             if (kt + 1 < nk) {
@@ -454,9 +451,9 @@ MG_DEVICE void bf16_tile(const GemmArgs& g, int tm, int tn, uint16_t* smem)
                 load(pa1, pb1, kt + 3 < nk ? kt + 3 : nk - 1);
                 panel(1, [&](int s) {
 #pragma unroll
-                    for (int q = s; q < PA::PER; q += STEPS) pa0.store_chunk(As[0][0], As[0][NL - 1], tid, q);
+                    for (int q = s; q < PA::PER; q += STEPS) pa0.store_chunk(As[0][0], tid, q);
 #pragma unroll
-                    for (int q = s; q < PB::PER; q += STEPS) pb0.store_chunk(Bs[0][0], Bs[0][NL - 1], tid, q);
+                    for (int q = s; q < PB::PER; q += STEPS) pb0.store_chunk(Bs[0][0], tid, q);
                 });
                 __syncthreads();
             }
