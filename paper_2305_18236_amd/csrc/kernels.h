@@ -93,13 +93,18 @@ struct BatchProblem {
 };
 
 // Tile variants of the persistent batched kernels, as configuration ids of
-// the single-GEMM tables: FP32 {64x64, 128x128}; BF16 paths {64x64, 128x64,
-// 128x128}.  All run 256 threads.  (A third FP32 variant would push the
-// persistent kernel past 256 registers per lane.)
+// the single-GEMM tables, whose results they equal bit for bit: FP32 {64x64,
+// 128x128} over 512 threads; BF16 paths {64x64, 128x64, 128x128} over 256.
 constexpr int kSgemmBatchedVariants = 2;
 constexpr int kBf16BatchedVariants = 3;
 extern const int kSgemmBatchedCfg[kSgemmBatchedVariants];
 extern const int kBf16BatchedCfg[kBf16BatchedVariants];
+// The tile each variant is run with.
+struct BatchedTile {
+    int bm, bn;
+};
+extern const BatchedTile kSgemmBatchedTile[kSgemmBatchedVariants];
+extern const BatchedTile kBf16BatchedTile[kBf16BatchedVariants];
 
 // counter: a device word holding 0 at launch (the work-list cursor).
 // stamps: nullptr, or 2 * grid words that receive each workgroup's start and

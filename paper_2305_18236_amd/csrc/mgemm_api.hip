@@ -986,18 +986,35 @@ int batched_count(int path)
     return path == MG_PATH_FP32 ? mg::kSgemmBatchedVariants : mg::kBf16BatchedVariants;
 }
 
-int choose_batched_variant(int path, int64_t M, int64_t N, int64_t K)
+// The variant the forced configuration or the tuning table names, or -1.
+int named_batched_variant(int path, int64_t M, int64_t N, int64_t K)
 {
     const int* cfgs = batched_cfgs(path);
-    const int nv = batched_count(path);
     int tuned = g_forced[path].load();
     if (tuned < 0) tuned = table_lookup(path, M, N, K, 1);
     if (tuned < 0) tuned = table_lookup(path, M, N, K, 0);
-    for (int v = 0; v < nv; ++v)
+    for (int v = 0; v < batched_count(path); ++v)
         if (cfgs[v] == tuned) return v;
-    if (M >= 128 && N >= 128) return nv - 1;   // 128 x 128
-    if (M >= 128 && nv == 3) return 1;         // 128 x 64
-    return 0;                                  // 64 x 64
+    return -1;
+}
+
+// Else the largest tile: waves outside C multiply nothing, so its padding
+// costs little (512 problems of 32 to 2048, us, 64-row tiles / 128 x 128: FP32
+// 1283 / 1191, bf16x3 1507 / 725, BF16 1018 / 583).  Only where one such tile
+// is long beside the `share` of all products that a workgroup gets would the
+// last tiles run alone; those problems take a smaller one.  (us, 128 x 128 ->
+// smaller: FP32 64 problems to 2048, tiles of up to 2.9 shares, 254 -> 156,
+// of 1.5 shares 295 -> 287, 512 problems to 512, 1.6 shares, 125 -> 130;
+// BF16 at 2.9 shares 99 -> 82 on 128 x 64, at 7.5 48 -> 46, at 15 33 -> 27 on
+// 64 x 64; bf16x3 at 3.5 shares 60 -> 69, at 6.9 89 -> 79, at 15 37 -> 30.)
+int choose_batched_variant(int path, int64_t M, int64_t N, int64_t K, double share)
+{
+    const int named = named_batched_variant(path, M, N, K);
+    if (named >= 0) return named;
+    const int last = batched_count(path) - 1;
+    const double shares = share > 0 ? 128.0 * 128.0 * double(K) / share : 0;
+    if (path == MG_PATH_FP32) return shares > 2 ? 0 : last;
+    return shares > 9 ? 0 : shares > (path == MG_PATH_BF16X3 ? 4 : 2.5) ? 1 : last;
 }
 
 // Compute units of the current device, queried once per device.  Threads
@@ -1576,7 +1593,7 @@ int mg_batched_config(int path, int64_t M, int64_t N, int64_t K)
 {
     if (!batched_path(path) || M < 0 || N < 0 || K < 0) return MG_ERR_UNSUPPORTED;
     if (beyond_int(M, N, K)) return MG_ERR_TOO_LARGE;
-    return batched_cfgs(path)[choose_batched_variant(path, M, N, K)];
+    return batched_cfgs(path)[choose_batched_variant(path, M, N, K, 0)];
 }
 
 size_t mg_gemm_batched_workspace_size(int path, int64_t count)
@@ -1612,16 +1629,20 @@ int run_batched(int path, int64_t count, const mg_problem* problems, void* works
         (reinterpret_cast<uintptr_t>(workspace) & 255) != 0)
         return MG_ERR_WORKSPACE;
 
-    const ConfigTable t = table_of(path);
-    const int* cfgs = batched_cfgs(path);
+    const mg::BatchedTile* shapes = path == MG_PATH_FP32 ? mg::kSgemmBatchedTile : mg::kBf16BatchedTile;
+    const int64_t slots = int64_t(device_cus()) * mg::batched_blocks_per_cu(path);
+    double share = 0;
+    for (int64_t i = 0; i < count; ++i)
+        share += double(problems[i].M) * double(problems[i].N) * double(problems[i].K);
+    share /= double(slots);
     std::vector<mg::BatchProblem> host;
     host.reserve(size_t(count));
     for (int64_t i = 0; i < count; ++i) {
         const mg_problem& q = problems[i];
         if (q.M == 0 || q.N == 0) continue;
         mg::BatchProblem b{};
-        b.variant = choose_batched_variant(path, q.M, q.N, q.K);
-        const mg::SgemmConfig& c = t.cfgs[cfgs[b.variant]];
+        b.variant = choose_batched_variant(path, q.M, q.N, q.K, share);
+        const mg::BatchedTile& c = shapes[b.variant];
         b.ta = is_t(q.transA);
         b.tb = is_t(q.transB);
         b.g.A = q.A; b.g.B = q.B; b.g.C = q.C;
@@ -1639,8 +1660,7 @@ int run_batched(int path, int64_t count, const mg_problem* problems, void* works
     if (host.empty()) return MG_OK;
     // longest tiles first
     std::stable_sort(host.begin(), host.end(), [&](const mg::BatchProblem& x, const mg::BatchProblem& y) {
-        const mg::SgemmConfig& cx = t.cfgs[cfgs[x.variant]];
-        const mg::SgemmConfig& cy = t.cfgs[cfgs[y.variant]];
+        const mg::BatchedTile &cx = shapes[x.variant], &cy = shapes[y.variant];
         return int64_t(cx.bm) * cx.bn * (x.g.K + 1) > int64_t(cy.bm) * cy.bn * (y.g.K + 1);
     });
     int64_t total = 0;
@@ -1653,7 +1673,6 @@ int run_batched(int path, int64_t count, const mg_problem* problems, void* works
     std::memcpy(upload.data() + kBatchedHeader, host.data(), host.size() * sizeof(mg::BatchProblem));
     hipError_t e = hipMemcpyAsync(workspace, upload.data(), upload.size(), hipMemcpyHostToDevice, s);
     if (e != hipSuccess) return hip_status(e);
-    const int64_t slots = int64_t(device_cus()) * mg::batched_blocks_per_cu(path);
     const int grid = int(std::min<int64_t>(total, slots));
     uint8_t* base = static_cast<uint8_t*>(workspace);
     if (grid_out) *grid_out = grid;

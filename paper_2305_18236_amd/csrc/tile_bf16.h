@@ -283,7 +283,9 @@ struct BfLoaderSel<true, ROWS, BK, LDR, NT, KSRC, TERMS> {
 // PACKED: g.A / g.B point at the planes of pre-packed op(A) / op(B)^T
 // (16-bit, row stride lda / ldb, zero-padded to whole tiles and panels), TA/TB
 // are ignored and no bounds checks are needed on the loads.
-template <int BM, int BN, int BK, int WM, int WN, bool TA, bool TB, int TERMS, bool PACKED = false>
+// SKIP: waves whose block of the tile lies outside C fetch and pack their
+// share of the panels but multiply nothing.
+template <int BM, int BN, int BK, int WM, int WN, bool TA, bool TB, int TERMS, bool PACKED = false, bool SKIP = false>
 MG_DEVICE void bf16_tile(const GemmArgs& g, int tm, int tn, uint16_t* smem)
 {
     constexpr int WAVES_N = BN / WN;
@@ -297,12 +299,16 @@ MG_DEVICE void bf16_tile(const GemmArgs& g, int tm, int tn, uint16_t* smem)
     uint16_t (*As)[NL][BM * LDR] = reinterpret_cast<uint16_t (*)[NL][BM * LDR]>(smem);
     uint16_t (*Bs)[NL][BN * LDR] = reinterpret_cast<uint16_t (*)[NL][BN * LDR]>(smem + 2 * NL * BM * LDR);
 
-    const int tid = threadIdx.x;
-    const int lane = tid & 63, wave = tid >> 6;
+    // (opaque, so that a persistent kernel does not keep what follows from it,
+    // for every variant it holds, in registers across its tiles)
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    const int lane = tid & 63, wave = SKIP ? __builtin_amdgcn_readfirstlane(tid >> 6) : tid >> 6;
     const int wm0 = (wave / WAVES_N) * WM, wn0 = (wave % WAVES_N) * WN;
     const int c = lane & 31, h = lane >> 5;
 
     const int64_t m0 = int64_t(tm) * BM, n0 = int64_t(tn) * BN;
+    const bool live = !SKIP || (m0 + wm0 < g.M && n0 + wn0 < g.N);
 
     typename BfLoaderSel<PACKED, BM, BK, LDR, NT, !TA, TERMS>::type pa;
     typename BfLoaderSel<PACKED, BN, BK, LDR, NT, TB, TERMS>::type pb;
@@ -470,7 +476,7 @@ MG_DEVICE void bf16_tile(const GemmArgs& g, int tm, int tn, uint16_t* smem)
         for (int kt = 0; kt < nk; ++kt) {
             const int cur = kt & 1;
             if (kt + 1 < nk) fetch(int64_t(kt + 1) * BK);
-            panel(cur, [](int) {});
+            if (live) panel(cur, [](int) {});
             // Keep the pack (which waits for this iteration's global loads)
             // after the MFMAs: the compiler may otherwise hoist the LDS writes
             // above them, since they target the other buffer.

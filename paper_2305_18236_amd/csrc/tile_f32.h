@@ -216,8 +216,13 @@ constexpr int sgemm_lds_floats() { return KG * 2 * BK * (BM + BN); }
 // through LDS (group 0 first, then 1, ...) before group 0's epilogue.  A
 // small tile then has KG waves per SIMD to hide latency with, without a
 // second launch for a split K.  (GEMM only: SYR2K keeps KG = 1.)
+//
+// SKIP: waves whose block of the tile lies outside C fetch and pack their
+// share of the panels but multiply nothing, which leaves the matrix cores to
+// the waves that share their SIMDs: a large tile then costs a small problem
+// little more than a small tile.
 template <int BM, int BN, int BK, int WM, int WN, bool TA, bool TB, bool SYR2K = false, int UPLO = 0,
-          bool DEEP = false, int KG = 1>
+          bool DEEP = false, int KG = 1, bool SKIP = false>
 MG_DEVICE void sgemm_tile(const GemmArgs& g, int tm, int tn, float* smem)
 {
     static_assert(KG == 1 || !SYR2K, "SYR2K runs one K group");
@@ -229,15 +234,19 @@ MG_DEVICE void sgemm_tile(const GemmArgs& g, int tm, int tn, float* smem)
     static_assert(H == 1 || H == 2 || H == 4, "WN must be 32, 64 or 128");
     static_assert(BK % 2 == 0, "BK must be a multiple of the MFMA depth");
 
+    // (opaque, so that a persistent kernel does not keep what follows from it,
+    // for every variant it holds, in registers across its tiles)
+    int thread = threadIdx.x;
+    asm volatile("" : "+v"(thread));
     // K group of this wave (uniform across the wave) and its LDS buffers
-    const int grp = KG > 1 ? __builtin_amdgcn_readfirstlane(int(threadIdx.x) / NT) : 0;
+    const int grp = KG > 1 ? __builtin_amdgcn_readfirstlane(thread / NT) : 0;
     float* gsmem = smem + grp * (2 * BK * (BM + BN));
     float (*As)[BK * BM] = reinterpret_cast<float (*)[BK * BM]>(gsmem);
     float (*Bs)[BK * BN] = reinterpret_cast<float (*)[BK * BN]>(gsmem + 2 * BK * BM);
 
-    const int tid = KG > 1 ? int(threadIdx.x) % NT : int(threadIdx.x);   // thread within the group
+    const int tid = KG > 1 ? thread % NT : thread;   // thread within the group
     const int lane = tid & 63;
-    const int wave = tid >> 6;
+    const int wave = SKIP ? __builtin_amdgcn_readfirstlane(tid >> 6) : tid >> 6;
     const int wm0 = (wave / WAVES_N) * WM;
     const int wn0 = (wave % WAVES_N) * WN;
     const int c = lane & 31;     // column of the MFMA operand / result
@@ -321,7 +330,8 @@ MG_DEVICE void sgemm_tile(const GemmArgs& g, int tm, int tn, float* smem)
     // Panel i, in LDS buffer cur: fetch panel i + AHEAD into set_cur (DEEP: its
     // panel i went to LDS one iteration ago), and pack panel i + 1 from
     // set_next half-way.
-    auto panel = [&](int i, int cur, auto set_cur, auto set_next, auto quick) {
+    // work: this wave's block is inside C (SKIP).
+    auto panel = [&](int i, int cur, auto set_cur, auto set_next, auto quick, auto work) {
         using SetNext = decltype(set_next);
         if constexpr (decltype(quick)::value) {
             fetch(panel_of(i + AHEAD), set_cur, quick);
@@ -332,6 +342,11 @@ MG_DEVICE void sgemm_tile(const GemmArgs& g, int tm, int tn, float* smem)
                 return;
             }
             if (panel_of(i + AHEAD) < p1) fetch(panel_of(i + AHEAD), set_cur, quick);
+        }
+        if constexpr (!decltype(work)::value) {
+            pack(cur ^ 1, SetNext{});
+            __syncthreads();
+            return;
         }
 
         const float* a_rows = As[cur] + h * BM;
@@ -382,28 +397,32 @@ MG_DEVICE void sgemm_tile(const GemmArgs& g, int tm, int tn, float* smem)
     // half of what the second staging set is for (us, before -> after: 8192^3
     // 7849 -> 7593, 1024^3 24.9 -> 23.4, SYR2K 2048 x 2048 183 -> 180).
     int i = 0;
-    auto two = [&](auto quick) {
-        panel(i, 0, Set0{}, Set1{}, quick);
-        if (decltype(quick)::value || i + 1 < iters) panel(i + 1, 1, Set1{}, Set0{}, quick);
+    auto two = [&](auto quick, auto work) {
+        panel(i, 0, Set0{}, Set1{}, quick, work);
+        if (decltype(quick)::value || i + 1 < iters) panel(i + 1, 1, Set1{}, Set0{}, quick, work);
         i += 2;
     };
-    while (i < iters) {
-        // group 0's panel; the last one fetched by two(Yes) is group KG - 1's
-        auto at = [&]() { return p0 + i * KG; };
-        int lim = nwhole;
-        if (SYR2K) {
-            if (at() >= nk) {   // (the offsets are not kept over both segments)
-                int t = tid;
-                asm volatile("" : "+v"(t));
-                oa = LA::offsets(g.ldb, m0, g.M, t);
-                ob = LB::offsets(g.lda, n0, g.N, t);
-                lim = nk + nwhole;
+    auto k_loop = [&](auto work) {
+        while (i < iters) {
+            // group 0's panel; the last one fetched by two(Yes) is group KG - 1's
+            auto at = [&]() { return p0 + i * KG; };
+            int lim = nwhole;
+            if (SYR2K) {
+                if (at() >= nk) {   // (the offsets are not kept over both segments)
+                    int t = tid;
+                    asm volatile("" : "+v"(t));
+                    oa = LA::offsets(g.ldb, m0, g.M, t);
+                    ob = LB::offsets(g.lda, n0, g.N, t);
+                    lim = nk + nwhole;
+                }
+                lim = min(lim, p1);
             }
-            lim = min(lim, p1);
+            while (at() + (AHEAD + 2) * KG - 1 < lim) two(Yes{}, work);
+            two(No{}, work);
         }
-        while (at() + (AHEAD + 2) * KG - 1 < lim) two(Yes{});
-        two(No{});
-    }
+    };
+    if (SKIP && !(m0 + wm0 < g.M && n0 + wn0 < g.N)) k_loop(No{});
+    else k_loop(Yes{});
     if constexpr (KG > 1) {
         // Add the groups' sums through LDS (free after the loop's last
         // barrier): group q > 0 stores its accumulators in turn, group 0
