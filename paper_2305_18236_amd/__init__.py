@@ -7,10 +7,15 @@ and streams; it computes nothing on the GEMM path.
 """
 from __future__ import annotations
 
+import ctypes
 import os
+import struct
 
 from . import _native
 from ._native import MgemmError, check, status_string  # noqa: F401
+
+# struct mg_problem (native alignment, as the ctypes mirror of it)
+_PROBLEM = struct.Struct("@cc3q2fPqPqPq")
 
 PATHS = {"fp32": 0, "bf16x3": 1, "bf16": 2, "fp8": 3, "fp16": 4}
 
@@ -31,9 +36,10 @@ def operand_layout(X):
     tensor is 'T' with ld = stride(1).  Any other stride pattern is rejected
     (no hidden copy is made).
     """
-    if X.dim() != 2:
+    shape = X.shape
+    if len(shape) != 2:
         raise ValueError("operands must be 2-D")
-    r, c = X.shape
+    r, c = shape
     s0, s1 = X.stride()
     # A stride only matters along a dimension longer than 1; where it matters
     # it is taken as it is (never raised), so a broadcast view (stride 0) or
@@ -50,15 +56,22 @@ def output_ld(C) -> int:
     overlap (a broadcast or otherwise aliased view) are refused, since the
     kernels would write past the tensor's storage."""
     M, N = C.shape
-    if C.stride(1) != 1 and N > 1:
+    s0, s1 = C.stride()
+    if s1 != 1 and N > 1:
         raise ValueError("C must have unit column stride")
-    if M > 1 and C.stride(0) < max(N, 1):
+    if M > 1 and s0 < max(N, 1):
         raise ValueError(f"C strides {C.stride()} make rows overlap")
-    return C.stride(0) if M > 1 else max(N, 1)
+    return s0 if M > 1 else max(N, 1)
+
+
+_TRANS = {"N": b"N", "T": b"T"}   # the C ABI's characters
 
 
 def _stream_ptr(device):
     import torch
+    if device.type == "cuda":
+        # the raw handle, without the Stream object around it (1 us a call)
+        return torch._C._cuda_getCurrentRawStream(device.index)
     return torch.cuda.current_stream(device).cuda_stream
 
 
@@ -82,26 +95,29 @@ def gemm(A, B, C=None, *, alpha: float = 1.0, beta: float = 0.0, path="fp32", wo
         if beta != 0.0:
             raise ValueError("beta != 0 needs an input C")
         C = torch.empty((M, N), dtype=torch.float32, device=A.device)
-    if C.dtype != torch.float32 or tuple(C.shape) != (M, N) or not C.is_cuda:
-        raise ValueError("C must be a float32 M x N GPU tensor")
-    if C.dim() != 2:
-        raise ValueError("C must be 2-D")
-    ldc = output_ld(C)
-    for X in (A, B):
-        if X.numel() and C.numel() and X.data_ptr() == C.data_ptr():
-            raise ValueError("C must not alias A or B")
+        ldc = max(N, 1)
+    else:
+        if C.dtype != torch.float32 or tuple(C.shape) != (M, N) or not C.is_cuda:
+            raise ValueError("C must be a float32 M x N GPU tensor")
+        ldc = output_ld(C)
+        for X in (A, B):
+            if X.numel() and C.numel() and X.data_ptr() == C.data_ptr():
+                raise ValueError("C must not alias A or B")
     tA, lda = operand_layout(A)
     tB, ldb = operand_layout(B)
+    tA, tB = _TRANS[tA], _TRANS[tB]
     pid = _path_id(path)
-    need = _native.mg_gemm_workspace_size(pid, tA, tB, M, N, K)
+    lib = _native.lib()
+    need = lib.mg_gemm_workspace_size(pid, tA, tB, M, N, K)
     ws_ptr, ws_bytes = None, 0
     if need:
         if workspace is None:
             workspace = torch.empty(need, dtype=torch.uint8, device=A.device)
         ws_ptr, ws_bytes = workspace.data_ptr(), workspace.numel() * workspace.element_size()
-    st = _native.mg_gemm(pid, tA, tB, M, N, K, float(alpha), A.data_ptr(), lda, B.data_ptr(), ldb,
-                         float(beta), C.data_ptr(), ldc, ws_ptr, ws_bytes, _stream_ptr(A.device))
-    check(st, "mg_gemm")
+    st = lib.mg_gemm(pid, tA, tB, M, N, K, float(alpha), A.data_ptr(), lda, B.data_ptr(), ldb, float(beta),
+                     C.data_ptr(), ldc, ws_ptr, ws_bytes, _stream_ptr(A.device))
+    if st != 0:
+        check(st, "mg_gemm")
     return C
 
 
@@ -150,24 +166,41 @@ def gemm_batched(problems, *, path="fp32", workspace=None):
     """
     import torch
     problems = list(problems)
+    f32 = torch.float32
     arr = (_native.mg_problem * max(len(problems), 1))()
-    dev = None
+    size = ctypes.sizeof(_native.mg_problem)
+    pack_into, at, dev = _PROBLEM.pack_into, 0, None
     for i, (A, B, C, alpha, beta) in enumerate(problems):
-        if A.dtype != torch.float32 or B.dtype != torch.float32 or C.dtype != torch.float32:
+        if A.dtype is not f32 or B.dtype is not f32 or C.dtype is not f32:
             raise TypeError("operands must be float32")
         M, K = A.shape
         K2, N = B.shape
-        if K2 != K or tuple(C.shape) != (M, N):
+        if K2 != K or C.shape != (M, N):
             raise ValueError(f"problem {i}: shapes {tuple(A.shape)} x {tuple(B.shape)} -> {tuple(C.shape)}")
+        # row-major matrices of several rows here, everything else (with the
+        # same answers for these) in output_ld and operand_layout
+        ldc, c1 = C.stride()
+        if not (c1 == 1 and ldc >= N > 0 and M > 1):
+            try:
+                ldc = output_ld(C)
+            except ValueError as e:
+                raise ValueError(f"problem {i}: {e}") from None
+        tA, tB = "N", "N"
+        lda, a1 = A.stride()
+        if not (a1 == 1 and lda >= K > 0 and M > 1):
+            tA, lda = operand_layout(A)
+        ldb, b1 = B.stride()
+        if not (b1 == 1 and ldb >= N > 0 and K > 1):
+            tB, ldb = operand_layout(B)
         try:
-            ldc = output_ld(C)
-        except ValueError as e:
-            raise ValueError(f"problem {i}: {e}") from None
-        tA, lda = operand_layout(A)
-        tB, ldb = operand_layout(B)
-        arr[i] = _native.mg_problem(tA.encode(), tB.encode(), M, N, K, float(alpha), float(beta),
-                                    A.data_ptr(), lda, B.data_ptr(), ldb, C.data_ptr(), ldc)
-        dev = A.device
+            pack_into(arr, at, _TRANS[tA], _TRANS[tB], M, N, K, alpha, beta, A.data_ptr(), lda, B.data_ptr(), ldb,
+                      C.data_ptr(), ldc)
+        except (struct.error, OverflowError, TypeError):   # an alpha or beta that only float() and ctypes take
+            arr[i] = _native.mg_problem(_TRANS[tA], _TRANS[tB], M, N, K, float(alpha), float(beta), A.data_ptr(), lda,
+                                        B.data_ptr(), ldb, C.data_ptr(), ldc)
+        at += size
+    if problems:
+        dev = problems[-1][0].device
     if not problems:
         return
     pid = _path_id(path)
