@@ -170,13 +170,126 @@ void gemm_bf16_direct_kernel(GemmArgs args)
                            [&](float a, float c0) { return beta != 0.f ? __builtin_fmaf(alpha, a, beta * c0) : alpha * a; });
 }
 
-template <int BM, int BN, int WM, int WN, int TERMS>
-static hipError_t launch_bf16_direct(GemmArgs g, hipStream_t stream)
+// The direct form through a ring of NS stages (ring_loop in tile_bytes.h), for
+// launches of at most one workgroup per compute unit.  Bit-identical.
+template <int BM, int BN, int WM, int WN, int TERMS, int NS>
+__global__ __launch_bounds__((BM / WM) * (BN / WN) * 64)
+void gemm_bf16_ring_kernel(GemmArgs args)
+{
+    constexpr int BK = TERMS == 3 ? 32 : 64;  // k per 128-byte panel row
+    constexpr int KBYTES = 128 / BK;          // bytes per k in a plane row
+    constexpr int STEPS = BK / 16;
+    constexpr int WAVES_N = BN / WN;
+    constexpr int NW = (BM / WM) * WAVES_N;
+    constexpr int V = WM / 32, H = WN / 32;
+
+    MG_RING_STAGES(NS, (BM + BN) * 128);
+
+    GemmArgs g = args;
+    int64_t kbyte0 = 0;
+    if (gridDim.y > 1) {
+        // split K: workgroup row s multiplies the range [s k_chunk, ...) and
+        // stores its unscaled partial product (reduced afterwards)
+        const int64_t k0 = int64_t(blockIdx.y) * g.k_chunk;
+        g.K = min(g.k_chunk, g.K - k0);
+        kbyte0 = KBYTES * k0;
+        g.C = g.part + int64_t(blockIdx.y) * g.part_stride;
+        g.ldc = g.ldp;
+        g.alpha = 1.f;
+        g.beta = 0.f;
+    }
+    const int tid = threadIdx.x;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm0 = (wave / WAVES_N) * WM, wn0 = (wave % WAVES_N) * WN;
+    const int c = lane & 31, h = lane >> 5;
+
+    int tm, tn;
+    tile_of(blockIdx.x, g.tiles_m, g.tiles_n, g.group_m, g.remap, tm, tn);
+    const int64_t m0 = int64_t(tm) * BM, n0 = int64_t(tn) * BN;
+    const uint8_t* __restrict__ qa =
+        reinterpret_cast<const uint8_t*>(reinterpret_cast<const uint16_t*>(g.A) + m0 * g.lda) + kbyte0;
+    const uint8_t* __restrict__ qb =
+        reinterpret_cast<const uint8_t*>(reinterpret_cast<const uint16_t*>(g.B) + n0 * g.ldb) + kbyte0;
+    const uint32_t lda32 = uint32_t(2 * g.lda), ldb32 = uint32_t(2 * g.ldb);
+
+    floatx16 acc[V][H];
+#pragma unroll
+    for (int i = 0; i < V; ++i)
+#pragma unroll
+        for (int j = 0; j < H; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+    auto chunk = [&](const uint8_t* L, int row, int g) { return __builtin_bit_cast(bf16x8, ring_chunk(L, row, g)); };
+    auto panel = [&](const uint8_t* LA, const uint8_t* LB) {
+#pragma unroll
+        for (int s = 0; s < STEPS; ++s) {
+            // lane (c, h) supplies k 16s + 8h .. +7 of row c: global chunk
+            // 2s + h (bf16x3: hi there, lo in chunk 4 + 2s + h)
+            if constexpr (TERMS == 3) {
+                bf16x8 ah[V], al[V], bh[H], bl[H];
+#pragma unroll
+                for (int j = 0; j < H; ++j) {
+                    bh[j] = chunk(LB, wn0 + 32 * j + c, 2 * s + h);
+                    bl[j] = chunk(LB, wn0 + 32 * j + c, 4 + 2 * s + h);
+                }
+#pragma unroll
+                for (int i = 0; i < V; ++i) {
+                    ah[i] = chunk(LA, wm0 + 32 * i + c, 2 * s + h);
+                    al[i] = chunk(LA, wm0 + 32 * i + c, 4 + 2 * s + h);
+                }
+#pragma unroll
+                for (int i = 0; i < V; ++i)
+#pragma unroll
+                    for (int j = 0; j < H; ++j) acc[i][j] = mfma16<3>(al[i], bh[j], acc[i][j]);
+#pragma unroll
+                for (int i = 0; i < V; ++i)
+#pragma unroll
+                    for (int j = 0; j < H; ++j) acc[i][j] = mfma16<3>(ah[i], bl[j], acc[i][j]);
+#pragma unroll
+                for (int i = 0; i < V; ++i)
+#pragma unroll
+                    for (int j = 0; j < H; ++j) acc[i][j] = mfma16<3>(ah[i], bh[j], acc[i][j]);
+            } else {
+                bf16x8 a[V], b[H];
+#pragma unroll
+                for (int i = 0; i < V; ++i) a[i] = chunk(LA, wm0 + 32 * i + c, 2 * s + h);
+#pragma unroll
+                for (int j = 0; j < H; ++j) b[j] = chunk(LB, wn0 + 32 * j + c, 2 * s + h);
+#pragma unroll
+                for (int i = 0; i < V; ++i)
+#pragma unroll
+                    for (int j = 0; j < H; ++j) acc[i][j] = mfma16<TERMS>(a[i], b[j], acc[i][j]);
+            }
+        }
+    };
+    ring_loop<NS, (BM + BN) * 8 / (NW * 64)>(
+        int((g.K + BK - 1) / BK),
+        [&](auto s, int kp) {
+            uint8_t* L = ring_stage(s);
+            direct_copy<BM, NW>(qa, lda32, uint32_t(kp) * 128u, L, wave, lane);
+            direct_copy<BN, NW>(qb, ldb32, uint32_t(kp) * 128u, L + BM * 128, wave, lane);
+        },
+        [&](auto s, int) { panel(ring_stage(s), ring_stage(s) + BM * 128); });
+
+    const float alpha = g.alpha, beta = g.beta;
+    store_acc_blocks<V, H>(g.C, g.ldc, g.M, g.N, m0 + wm0, n0 + wn0, h, c, beta != 0.f, acc,
+                           [&](float a, float c0) { return beta != 0.f ? __builtin_fmaf(alpha, a, beta * c0) : alpha * a; });
+}
+
+template <int BM, int BN, int WM, int WN, int TERMS, int RING = 0>
+static hipError_t launch_bf16_direct(GemmArgs g, hipStream_t stream, int cus)
 {
     constexpr int NT = (BM / WM) * (BN / WN) * 64;
     g.tiles_m = int((g.M + BM - 1) / BM);
     g.tiles_n = int((g.N + BN - 1) / BN);
     const dim3 grid(g.tiles_m * g.tiles_n, split_count(g)), block(NT);
+    if constexpr (RING > 0) {
+        if (int64_t(grid.x) * grid.y <= cus) {
+            hipLaunchKernelGGL((gemm_bf16_ring_kernel<BM, BN, WM, WN, TERMS, RING>), grid, block, 0, stream, g);
+            return hipGetLastError();
+        }
+    }
     hipLaunchKernelGGL((gemm_bf16_direct_kernel<BM, BN, WM, WN, TERMS>), grid, block, 0, stream, g);
     return hipGetLastError();
 }
@@ -234,7 +347,7 @@ const SgemmConfig kBf16Configs[] = {
 const int kNumBf16Configs = sizeof(kBf16Configs) / sizeof(kBf16Configs[0]);
 
 template <int TERMS>
-static hipError_t launch_terms(int cfg, bool ta, bool tb, GemmArgs g, hipStream_t stream, bool packed)
+static hipError_t launch_terms(int cfg, bool ta, bool tb, GemmArgs g, hipStream_t stream, bool packed, int cus)
 {
     switch (cfg) {
     case 0: return launch_bf16_cfg<256, 256, 32, 128, 128, TERMS>(ta, tb, g, stream, packed);
@@ -244,29 +357,29 @@ static hipError_t launch_terms(int cfg, bool ta, bool tb, GemmArgs g, hipStream_
     case 4: return launch_bf16_cfg<64, 64, 32, 32, 32, TERMS>(ta, tb, g, stream, packed);
     case 5: return launch_bf16_cfg<128, 64, 32, 64, 32, TERMS>(ta, tb, g, stream, packed);
     case 6:
-        if (packed) return launch_bf16_direct<256, 256, 128, 64, TERMS>(g, stream);
+        if (packed) return launch_bf16_direct<256, 256, 128, 64, TERMS>(g, stream, cus);
         return launch_bf16_cfg<256, 256, 32, 128, 64, TERMS>(ta, tb, g, stream, packed);
     case 7:
-        if (packed) return launch_bf16_direct<128, 128, 64, 64, TERMS>(g, stream);
+        if (packed) return launch_bf16_direct<128, 128, 64, 64, TERMS>(g, stream, cus);
         return launch_bf16_cfg<128, 128, 32, 64, 64, TERMS>(ta, tb, g, stream, packed);
     case 8: return launch_bf16_cfg<128, 128, 32, 64, 32, TERMS>(ta, tb, g, stream, packed);
     case 9: return launch_bf16_cfg<128, 128, 32, 32, 64, TERMS>(ta, tb, g, stream, packed);
     case 10:
-        if (packed) return launch_bf16_direct<128, 128, 64, 32, TERMS>(g, stream);
+        if (packed) return launch_bf16_direct<128, 128, 64, 32, TERMS, 5>(g, stream, cus);
         return launch_bf16_cfg<128, 128, 32, 64, 32, TERMS>(ta, tb, g, stream, packed);
     case 11:
-        if (packed) return launch_bf16_direct<256, 256, 64, 64, TERMS>(g, stream);
+        if (packed) return launch_bf16_direct<256, 256, 64, 64, TERMS>(g, stream, cus);
         return launch_bf16_cfg<256, 256, 32, 128, 64, TERMS>(ta, tb, g, stream, packed);
     default: return hipErrorInvalidValue;
     }
 }
 
-hipError_t launch_gemm_bf16(int terms, int cfg, bool ta, bool tb, GemmArgs g, hipStream_t stream, bool packed)
+hipError_t launch_gemm_bf16(int terms, int cfg, bool ta, bool tb, GemmArgs g, hipStream_t stream, bool packed, int cus)
 {
     switch (terms) {
-    case 1: return launch_terms<1>(cfg, ta, tb, g, stream, packed);
-    case 3: return launch_terms<3>(cfg, ta, tb, g, stream, packed);
-    case 16: return launch_terms<16>(cfg, ta, tb, g, stream, packed);
+    case 1: return launch_terms<1>(cfg, ta, tb, g, stream, packed, cus);
+    case 3: return launch_terms<3>(cfg, ta, tb, g, stream, packed, cus);
+    case 16: return launch_terms<16>(cfg, ta, tb, g, stream, packed, cus);
     default: return hipErrorInvalidValue;
     }
 }

@@ -70,8 +70,8 @@ extern const int kNumBf16Configs;
 
 // terms == 1: plain BF16; terms == 3: bf16x3 split.  packed: g.A / g.B are
 // the planes written by launch_bf16_pack.
-hipError_t launch_gemm_bf16(int terms, int cfg, bool ta, bool tb, GemmArgs g, hipStream_t stream,
-                            bool packed = false);
+// cus: the device's compute units.
+hipError_t launch_gemm_bf16(int terms, int cfg, bool ta, bool tb, GemmArgs g, hipStream_t stream, bool packed, int cus);
 // kind 1: bf16, 16: binary16 rows of Kp elements; 3: bf16x3's two terms
 // interleaved, rows of 2 Kp.
 hipError_t launch_bf16_pack(int kind, const PackOperand* ops, int count, int64_t Kd, int64_t Kp, hipStream_t stream);

@@ -232,6 +232,7 @@ int auto_splits(int64_t t, int64_t K)
 // ladder there (bf16x3 at the same shape: 222 us with 256 x 256 tiles, 303 us
 // with 64 x 64).
 bool uses_planes(int path, int cfg, int64_t M, int64_t N, int64_t K);
+constexpr int64_t kMaxPrepackK = int64_t(1) << 21;   // longest K of the pre-packed planes (see uses_planes)
 
 // The tile ladder (see choose_config): the largest tile whose tiles, times
 // the automatic split, give every compute unit a workgroup.
@@ -320,8 +321,18 @@ int ladder_choice(int path, int64_t M, int64_t N, int64_t K, int64_t cus, bool s
             // -> 81.2, 4096 x 5120 x 4096 548.5 -> 462.8; none slower by over
             // 2 %).
             const int64_t n128 = tiles(M, N, t.cfgs[ladder[1]].bm, t.cfgs[ladder[1]].bn);
+            // With at most one workgroup per compute unit the direct-copy tile
+            // now runs through a ring of LDS stages (ring_loop in tile_bytes.h),
+            // which moves that bound down to half the compute units for short
+            // ranges and, for BF16 and FP16, to seven twelfths up to 1200
+            // deep (us, split -> 10 unsplit: BF16 1748 x 1253 x 2410 on 140
+            // tiles 52.1 -> 32.5, 1031 x 2495 x 4208 on 180 74.8 -> 53.1, 2849
+            // x 959 x 5469 on 184 83.5 -> 71.1; bf16x3 2323 x 1032 x 1963 on
+            // 171 65.6 -> 49.3, 1181 x 1821 x 2437 on 150 74.2 -> 60.5, but
+            // 1445 x 1685 x 4921 on 168 level).
             if (i == 0 && s16 > 1 && (path != MG_PATH_BF16X3 || K / s16 < 2048) &&
-                (n128 >= cus || (n128 * 4 >= cus * 3 && K / s16 <= (path == MG_PATH_BF16X3 ? 512 : 1024))))
+                (n128 >= cus || (n128 * 2 >= cus && K / s16 <= 512) ||
+                 (path != MG_PATH_BF16X3 && n128 * 12 >= cus * 7 && K / s16 <= 1200)))
                 return uses_planes(path, 10, M, N, K) ? 10 : ladder[1];
             if (i == 0 && s16 == 1 && n > cus && n < 2 * cus && (n - cus) * (path == MG_PATH_BF16X3 ? 3 : 4) < cus)
                 return uses_planes(path, 10, M, N, K) ? 10 : ladder[1];
@@ -616,6 +627,114 @@ int fp8_small_config(int64_t M, int64_t N, int64_t K, int64_t cus)
     return best;
 }
 
+// ---- 16-bit outputs of fewer 128 x 128 tiles than half the compute units (and
+// no side under 384): the ladder's tiles there are large ones cut into many K
+// ranges, planned before the direct-copy tile had its ring of stages.  A time
+// model of the candidates replaces the ladder's plan where it predicts a
+// clear gain (5 %; bf16x3 15 %, whose model is less exact: at 1024^3 it
+// prefers 64 x 64 tiles in four ranges by 14 %, measured level with the
+// ladder's 128 x 128).  Per 32 k a workgroup takes the longer of `lat` (`latp`
+// on pre-packed planes) and `rate` per 128 x 128 outputs and resident
+// workgroup; a round costs c0 more; packing the planes and reducing a split
+// cost their launch and their traffic.  Constants fitted to 125 random shapes
+// per path with 25-40 plans each (device time of whole calls): the model's pick
+// is within 3 % (bf16x3 5 %) of the best plan in geometric mean, and 9 % (16 %)
+// faster than the ladder's (us: BF16 952 x 978 x 5977 52.8 -> 41, 398 x 1014 x
+// 4961 39.9 -> 34.6; bf16x3 893 x 907 x 2602 50.6 -> 42, 650 x 1056 x 1127 29.3
+// -> 21, 441 x 2667 x 472 26.1 -> 22).
+struct FewTile {
+    int cfg, bm, occ;
+    float lat, c0, rate, latp;
+};
+struct FewModel {
+    FewTile tile[4];
+    float base, pack_us, pack_rate, pack_bytes, red_us, red_rate;   // rates in MB per us
+};
+const FewModel kFew16 = {{{10, 128, 1, 0.901f, 0.203f, 0.186f, 0.087f}, {9, 128, 2, 0.959f, 0.241f, 0.213f, 0.294f},
+                          {4, 64, 4, 0.678f, 0.005f, 0.378f, 0.211f}, {11, 256, 1, 1.571f, 4.55f, 0.136f, 0.494f}},
+                         7.41f, 3.44f, 5.77f, 6.f, 1.60f, 3.69f};
+const FewModel kFewX3 = {{{10, 128, 1, 1.061f, 0.005f, 0.332f, 0.011f}, {2, 128, 2, 1.179f, 2.154f, 0.664f, 1.188f},
+                          {4, 64, 4, 0.844f, 1.032f, 0.065f, 0.088f}, {1, 256, 1, 0.870f, 5.06f, 0.635f, 0.5f}},
+                         7.68f, 6.63f, 4.16f, 8.f, 1.27f, 3.29f};
+
+bool few_tiles(int path, int64_t M, int64_t N, int64_t K, int64_t cus)
+{
+    return is_16bit(path) && std::min(M, N) >= 384 && K >= 1 && K <= kMaxPrepackK && 2 * tiles(M, N, 128, 128) < cus;
+}
+
+float few_us(int path, const FewModel& m, const FewTile& c, int64_t M, int64_t N, int64_t K, int64_t s, float cus)
+{
+    const bool planes = uses_planes(path, c.cfg, M, N, K);
+    const float chunk = s > 1 ? float(round_up((K + s - 1) / s, kSplitGrain)) : float(K);
+    const float steps = std::ceil(chunk / 32.f);
+    const float per_cu = std::ceil(float(tiles(M, N, c.bm, c.bm)) * float(s) / cus);
+    const float full = std::floor(per_cu / float(c.occ)), rem = per_cu - full * float(c.occ);
+    const float lat = steps * (planes ? c.latp : c.lat), work = steps * c.rate * float(c.bm * c.bm) / 16384.f;
+    float t = m.base + full * (c.c0 + std::max(lat, float(c.occ) * work));
+    if (rem > 0.f) t += c.c0 + std::max(lat, rem * work);
+    const float mn = float(M) * float(N);
+    if (planes) t += m.pack_us + float(M + N) * float(K) * m.pack_bytes / (m.pack_rate * 1e6f);
+    if (s > 1) t += m.red_us + 4.f * float(s + 1) * mn / (m.red_rate * 1e6f);
+    return t;
+}
+
+// ladder: the ladder's configuration.  splits -1: its automatic split.
+Fp32Plan few_plan(int path, int64_t M, int64_t N, int64_t K, int ladder, bool split_ok)
+{
+    // (the thread's last shape: see small_plan)
+    struct Memo {
+        int64_t M, N, K, cus;
+        int path, ladder;
+        bool split_ok;
+        Fp32Plan plan;
+    };
+    static thread_local Memo memo{-1, -1, -1, -1, -1, -1, false, {0, 1}};
+    const int64_t cus = device_cus();
+    if (memo.M == M && memo.N == N && memo.K == K && memo.cus == cus && memo.path == path && memo.ladder == ladder &&
+        memo.split_ok == split_ok)
+        return memo.plan;
+    const bool x3 = path == MG_PATH_BF16X3;
+    const FewModel& m = x3 ? kFewX3 : kFew16;
+    // the ladder's plan, as one of the modelled tiles (6 and 11 are the 256 x
+    // 256 tile on planes, 1 without; 8 and 9 the same tile)
+    Fp32Plan best{ladder, -1};
+    float best_us = 1e30f;
+    const int bm = table_of(path).cfgs[ladder].bm;
+    for (const FewTile& c : m.tile)
+        if (c.cfg == ladder || (c.cfg != 10 && c.bm == bm)) {
+            const int64_t s = split_ok ? effective_splits(K, splits_16bit(tiles(M, N, bm, bm), K, cus)) : 1;
+            best_us = std::min(best_us, (x3 ? 0.85f : 0.95f) * few_us(path, m, c, M, N, K, s, float(cus)));
+        }
+    const int64_t most = split_ok ? std::min<int64_t>(kMaxSplits, K / kSplitGrain) : 1;
+    for (int64_t s = 1; s <= std::max<int64_t>(most, 1); ++s) {
+        if (s > 1 && effective_splits(K, s) != s) continue;
+        for (const FewTile& c : m.tile) {
+            const float us = few_us(path, m, c, M, N, K, s, float(cus));
+            if (us < best_us) {
+                best = Fp32Plan{c.cfg == 11 && !uses_planes(path, 11, M, N, K) ? 1 : c.cfg, int(s)};
+                best_us = us;
+            }
+        }
+    }
+    memo = Memo{M, N, K, cus, path, ladder, split_ok, best};
+    return best;
+}
+
+// The ladder's choice of a 16-bit path, with BF16's and FP16's 128 x 128 tile
+// over eight waves.
+int ladder_16bit(int path, int64_t M, int64_t N, int64_t K, bool split_ok)
+{
+    const int pick = ladder_choice(path, M, N, K, device_cus(), split_ok);
+    // BF16 and FP16 (one product per step) run the 128 x 128 tile as eight
+    // 32 x 64 waves (9): two waves per SIMD where configuration 2 has one,
+    // 4-10 % faster at every shape measured (us, configuration 2 -> 9, the
+    // same K ranges: 1024^3 26.3 -> 22.6, 2048^3 43.0 -> 39.9, 2048 x 2048 x
+    // 1024 30.1 -> 26.9, 2048 x 2048 x 8192 125.9 -> 113.1).  bf16x3's three
+    // products per step keep four waves busy (2048^3 in two K ranges: 70.1
+    // us against 77.2-78.4 with eight).
+    return pick == 2 && path != MG_PATH_BF16X3 ? 9 : pick;
+}
+
 int choose_config(int path, int64_t M, int64_t N, int64_t K, bool split_ok)
 {
     const int64_t cus = device_cus();
@@ -679,16 +798,11 @@ int choose_config(int path, int64_t M, int64_t N, int64_t K, bool split_ok)
     if (path == MG_PATH_FP32 && std::max({M, N, K}) <= 32) return 8;
     if (path == MG_PATH_FP32 && M > 0 && N > 0 && K > 0 && small_or_skinny(M, N, cus))
         return small_plan(M, N, K, split_ok).cfg;
+    if (is_16bit(path)) {
+        const int pick = ladder_16bit(path, M, N, K, split_ok);
+        return few_tiles(path, M, N, K, cus) ? few_plan(path, M, N, K, pick, split_ok).cfg : pick;
+    }
     const int pick = ladder_choice(path, M, N, K, cus, split_ok);
-    // BF16 and FP16 (one product per step) run the 128 x 128 tile as eight
-    // 32 x 64 waves (9): two waves per SIMD where configuration 2 has one,
-    // 4-10 % faster at every shape measured (us, configuration 2 -> 9, the
-    // same K ranges: 1024^3 26.3 -> 22.6, 2048^3 43.0 -> 39.9, 2048 x 2048 x
-    // 1024 30.1 -> 26.9, 2048 x 2048 x 8192 125.9 -> 113.1).  bf16x3's three
-    // products per step keep four waves busy (2048^3 in two K ranges: 70.1
-    // us against 77.2-78.4 with eight).
-    if (pick == 2 && (path == MG_PATH_BF16 || path == MG_PATH_FP16)) return 9;
-    if (path != MG_PATH_FP32) return pick;
     const Fp32Plan fp = fp32_plan(M, N, K, pick, split_ok);
     return fp32_small_tile(fp.cfg, M, N, K, fp.splits, split_ok);
 }
@@ -733,7 +847,6 @@ Fp8Workspace fp8_workspace(int64_t M, int64_t N, int64_t K)
 // 256 rows of up to 4 bytes per k (bf16x3's interleaved terms) stay within
 // 2^31 bytes; longer K converts in the kernel, whose loads fall back to
 // 64-bit addressing.
-constexpr int64_t kMaxPrepackK = int64_t(1) << 21;
 
 bool bf16_prepack_pays(int path, int64_t M, int64_t N, int64_t K)
 {
@@ -796,6 +909,10 @@ SplitPlan split_plan(int path, int cfg, int64_t M, int64_t N, int64_t K, bool sp
         if (fp.cfg == cfg || (fp.cfg == 3 && (cfg == 12 || cfg == 15)) || (fp.cfg == 5 && cfg == 17) ||
             (fp.cfg == 0 && cfg == 18) || (fp.cfg == 4 && cfg == 20))
             s = fp.splits;
+    }
+    if (s < 0 && few_tiles(path, M, N, K, device_cus())) {
+        const Fp32Plan fp = few_plan(path, M, N, K, ladder_16bit(path, M, N, K, true), true);
+        if (fp.cfg == cfg) s = fp.splits;
     }
     if (s < 0) s = path == MG_PATH_FP32 ? auto_splits(tiles(M, N, c.bm, c.bn), K)
                                         : splits_16bit(tiles(M, N, c.bm, c.bn), K, device_cus());
@@ -957,7 +1074,7 @@ int run_gemm(int path, bool ta, bool tb, int64_t M, int64_t N, int64_t K, float 
     case MG_PATH_BF16:
     case MG_PATH_FP16: {
         const int terms = kind_of(path);
-        if (bf16_planes == nullptr) return finish(mg::launch_gemm_bf16(terms, cfg, ta, tb, g, stream));
+        if (bf16_planes == nullptr) return finish(mg::launch_gemm_bf16(terms, cfg, ta, tb, g, stream, false, device_cus()));
         // pack each operand once, then multiply the packed planes
         const Bf16Workspace w = bf16_workspace(path, M, N, K);
         uint8_t* base = static_cast<uint8_t*>(bf16_planes);
@@ -969,7 +1086,7 @@ int run_gemm(int path, bool ta, bool tb, int64_t M, int64_t N, int64_t K, float 
         g.A = reinterpret_cast<const float*>(base + w.a);
         g.B = reinterpret_cast<const float*>(base + w.b);
         g.lda = g.ldb = terms == 3 ? 2 * w.Kp : w.Kp;   // both terms in one plane
-        return finish(mg::launch_gemm_bf16(terms, cfg, false, true, g, stream, true));
+        return finish(mg::launch_gemm_bf16(terms, cfg, false, true, g, stream, true, device_cus()));
     }
     default: return MG_ERR_UNSUPPORTED;
     }

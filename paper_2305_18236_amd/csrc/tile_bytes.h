@@ -4,6 +4,9 @@
 // (row stride ldq bytes, zero-padded so no bounds checks are needed), copied
 // through registers into LDS rows of LDR bytes.  Eight lanes copy one
 // 128-byte row with 16-byte accesses.
+#include <type_traits>
+#include <utility>
+
 #include "common.h"
 
 namespace mg {
@@ -105,6 +108,83 @@ MG_DEVICE void direct_copy(const uint8_t* __restrict__ q, uint32_t ld32, uint32_
 MG_DEVICE uint4 direct_chunk(const uint8_t* lds, int row, int g)
 {
     return *reinterpret_cast<const uint4*>(lds + row * 128 + 16 * (g ^ direct_swz(row)));
+}
+
+// ---- Ring form of the direct copies: NS stages, NS - 1 panels ahead.  Where
+// a launch gives a compute unit one workgroup only, nothing else runs while
+// it waits for a panel, and the two-buffer form, whose copy has one panel's
+// products (about 0.2 us on a 128 x 128 tile) to land in, waits out most of
+// each copy's latency.  Here a copy has NS - 1 panels' time.
+//
+// One barrier per panel: past it every wave's share of panel kt has landed
+// (each wave waited for its own copies, and only for those of this panel) and
+// every wave is done reading panel kt - 1, whose stage takes the next copy.
+template <int... I, class F>
+MG_DEVICE void each_of(std::integer_sequence<int, I...>, F f)
+{
+    (f(std::integral_constant<int, I>{}), ...);
+}
+
+// copy(stage, panel): issue this wave's PER copies of a panel into a stage;
+// compute(stage, panel): multiply it.  stage: an integral_constant, so that
+// each stage can be an array of its own (the compiler then tells the copies
+// into one from the reads of another).
+template <int NS, int PER, class Copy, class Compute>
+MG_DEVICE void ring_loop(int nk, Copy copy, Compute compute)
+{
+    static_assert((NS - 2) * PER < 64, "the wait counts the copies in flight");
+    auto turn = [&](auto stage, int kt, auto more) {
+        constexpr bool MORE = decltype(more)::value;
+        constexpr int S = decltype(stage)::value;
+        constexpr int FLY = MORE ? (NS - 2) * PER : 0;   // copies of newer panels
+        // vmcnt(FLY) lgkmcnt(0)
+        __builtin_amdgcn_s_waitcnt(0x0070 | (FLY & 15) | (FLY >> 4 << 14));
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        if constexpr (MORE) copy(std::integral_constant<int, (S + NS - 1) % NS>{}, kt + NS - 1);
+        compute(stage, kt);
+    };
+    using Yes = std::integral_constant<bool, true>;
+    using No = std::integral_constant<bool, false>;
+    // (with fewer panels than stages the last one again, for the same reason)
+    each_of(std::make_integer_sequence<int, NS - 1>{}, [&](auto s) { copy(s, min(decltype(s)::value, nk - 1)); });
+    // NS panels at a time, so that each one's stage is a compile-time choice,
+    // and without a branch while panels remain to be copied (with one the
+    // compiler waits for every copy in flight)
+    int kt = 0;
+    for (; kt + 2 * NS - 2 < nk; kt += NS)
+        each_of(std::make_integer_sequence<int, NS>{}, [&](auto s) { turn(s, kt + decltype(s)::value, Yes{}); });
+    each_of(std::make_integer_sequence<int, 2 * NS - 2>{}, [&](auto t) {
+        constexpr int T = decltype(t)::value;
+        const std::integral_constant<int, T % NS> s{};
+        if (kt + T + NS - 1 < nk) turn(s, kt + T, Yes{});
+        else if (kt + T < nk) turn(s, kt + T, No{});
+    });
+}
+
+// The LDS of a ring: one array per stage, picked by stage number.
+#define MG_RING_STAGES(NS, BYTES)                                                       \
+    __shared__ __attribute__((aligned(1024))) uint8_t ring0_[BYTES];                    \
+    __shared__ __attribute__((aligned(1024))) uint8_t ring1_[BYTES];                    \
+    __shared__ __attribute__((aligned(1024))) uint8_t ring2_[BYTES];                    \
+    __shared__ __attribute__((aligned(1024))) uint8_t ring3_[(NS) > 3 ? (BYTES) : 16];  \
+    __shared__ __attribute__((aligned(1024))) uint8_t ring4_[(NS) > 4 ? (BYTES) : 16];  \
+    auto ring_stage = [&](auto s) -> uint8_t* {                                         \
+        constexpr int S = decltype(s)::value;                                           \
+        if constexpr (S == 0) return ring0_;                                            \
+        else if constexpr (S == 1) return ring1_;                                       \
+        else if constexpr (S == 2) return ring2_;                                       \
+        else if constexpr (S == 3) return ring3_;                                       \
+        else return ring4_;                                                             \
+    }
+
+// Global chunk g of row `row` of a stage's panel, as one 16-byte vector load (as
+// a struct of words some of the reads lose what tells them from the copies in
+// flight).
+MG_DEVICE uintx4 ring_chunk(const uint8_t* lds, int row, int g)
+{
+    return *reinterpret_cast<const uintx4*>(lds + row * 128 + 16 * (g ^ direct_swz(row)));
 }
 
 }  // namespace mg
