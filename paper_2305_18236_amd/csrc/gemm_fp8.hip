@@ -572,6 +572,77 @@ static hipError_t launch_fp8_direct(Fp8Args g, hipStream_t stream)
     return hipGetLastError();
 }
 
+// The direct form through a ring of NS stages (ring_loop in tile_bytes.h), for
+// launches of at most one workgroup per compute unit.  The tile lies in one
+// 128-row scale block of each operand, whose scale bytes lane l holds for
+// panel l: K up to 64 panels.  Bit-identical to the two-buffer form.  GEMM only,
+// us, two buffers -> ring: 2048^3 17.5 -> 14.6, 1300 x 1300 x 5000 35.3 -> 23.9,
+// 1500^3 13.9 -> 11.6, 64 x 8192 x 8192 45.5 -> 26.8.
+template <int WM, int WN, int NS>
+__global__ __launch_bounds__((128 / WM) * (128 / WN) * 64)
+void gemm_fp8_ring_kernel(Fp8Args g)
+{
+    constexpr int BM = 128, BN = 128;
+    constexpr int WAVES_N = BN / WN;
+    constexpr int NW = (BM / WM) * WAVES_N;
+    constexpr int V = WM / 32, H = WN / 32;
+    MG_RING_STAGES(NS, (BM + BN) * 128);
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm0 = (wave / WAVES_N) * WM, wn0 = (wave % WAVES_N) * WN;
+    const int c = lane & 31, h = lane >> 5;
+    int tm, tn;
+    tile_of(blockIdx.x, g.tiles_m, g.tiles_n, g.group_m, g.remap, tm, tn);
+    const int64_t m0 = int64_t(tm) * BM, n0 = int64_t(tn) * BN;
+    const uint8_t* __restrict__ qa = g.qA + m0 * g.ldq;
+    const uint8_t* __restrict__ qb = g.qB + n0 * g.ldq;
+    const uint32_t ld32 = uint32_t(g.ldq);
+    const int nk = int(g.Kp / 128);
+    int scale_a = g.sA[tm * g.lds + min(lane, nk - 1)], scale_b = g.sB[tn * g.lds + min(lane, nk - 1)];
+    asm volatile("" : "+v"(scale_a), "+v"(scale_b));
+
+    floatx16 acc[V][H];
+#pragma unroll
+    for (int i = 0; i < V; ++i)
+#pragma unroll
+        for (int j = 0; j < H; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    auto frag = [&](const uint8_t* L, int row, int s) {
+        const uintx4 lo = ring_chunk(L, row, 4 * s + 2 * h), hi = ring_chunk(L, row, 4 * s + 2 * h + 1);
+        return intx8{int(lo[0]), int(lo[1]), int(lo[2]), int(lo[3]), int(hi[0]), int(hi[1]), int(hi[2]), int(hi[3])};
+    };
+    ring_loop<NS, (BM + BN) * 8 / (NW * 64)>(
+        nk,
+        [&](auto s, int kp) {
+            uint8_t* L = ring_stage(s);
+            direct_copy<BM, NW>(qa, ld32, uint32_t(kp) * 128u, L, wave, lane);
+            direct_copy<BN, NW>(qb, ld32, uint32_t(kp) * 128u, L + BM * 128, wave, lane);
+        },
+        [&](auto s, int kp) {
+            const uint8_t* L = ring_stage(s);
+            const int sa = __builtin_amdgcn_readlane(scale_a, kp), sb = __builtin_amdgcn_readlane(scale_b, kp);
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                intx8 a[V], b[H];
+#pragma unroll
+                for (int i = 0; i < V; ++i) a[i] = frag(L, wm0 + 32 * i + c, t);
+#pragma unroll
+                for (int j = 0; j < H; ++j) b[j] = frag(L + BM * 128, wn0 + 32 * j + c, t);
+#pragma unroll
+                for (int i = 0; i < V; ++i)
+#pragma unroll
+                    for (int j = 0; j < H; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a[i], b[j], acc[i][j], 0, 0, 0, sa,
+                                                                                    0, sb);
+            }
+        });
+    const float alpha = g.alpha, beta = g.beta;
+    store_acc_blocks<V, H>(g.C, g.ldc, g.M, g.N, m0 + wm0, n0 + wn0, h, c, beta != 0.f, acc,
+                           [&](float a, float c0) { return beta != 0.f ? __builtin_fmaf(alpha, a, beta * c0) : alpha * a; });
+}
+
 // Few rows (a decode step: tens of rows of activations against weights packed
 // once): reading the weights bounds it, so the work is cut to keep as many
 // bytes in flight on as many compute units as it can.  A workgroup owns a BM x
@@ -589,11 +660,8 @@ static hipError_t launch_fp8_direct(Fp8Args g, hipStream_t stream)
 template <int BM, int BN, int NW>
 __global__ __launch_bounds__(NW * 64) void gemm_fp8_skinny_kernel(Fp8Args g)
 {
-    constexpr int NS = 2;                           // stages of a wave's ring
     constexpr int V = BM / 32, H = BN / 32;
     constexpr int STAGE = (BM + BN) * 128;          // bytes of one wave's stage
-    constexpr int COPIES = (BM + BN) / 8;           // copy instructions per stage
-    static_assert((NS - 1) * COPIES < 64, "the wait counts the copies in flight");
     // one array per stage, so that the compiler can tell the copies into one
     // from the reads of another
     __shared__ __attribute__((aligned(1024))) uint8_t S0[NW * STAGE];
@@ -622,92 +690,48 @@ __global__ __launch_bounds__(NW * 64) void gemm_fp8_skinny_kernel(Fp8Args g)
     const int nk = int(g.Kp / 128);
     // this wave's panels: wave, wave + NW, ...
     const int n = nk > wave ? (nk - wave + NW - 1) / NW : 0;
-    auto copy = [&](uint8_t* S, int i) {
-        uint8_t* L = S + wave * STAGE;
-        const uint32_t k0 = uint32_t(wave + i * NW) * 128u;
-        direct_copy<BM, 1>(qa, ld32, k0, L, 0, lane);
-        direct_copy<BN, 1>(qb, ld32, k0, L + BM * 128, 0, lane);
-    };
-    // (one 16-byte vector load each: as a struct of four words some of the
-    // reads lose what tells them from the copies in flight, and wait for all)
     auto frag = [&](const uint8_t* L, int row, int s) {
-        const int g0 = 4 * s + 2 * h;
-        const uintx4 lo = *reinterpret_cast<const uintx4*>(L + row * 128 + 16 * (g0 ^ direct_swz(row)));
-        const uintx4 hi = *reinterpret_cast<const uintx4*>(L + row * 128 + 16 * ((g0 + 1) ^ direct_swz(row)));
+        const uintx4 lo = ring_chunk(L, row, 4 * s + 2 * h), hi = ring_chunk(L, row, 4 * s + 2 * h + 1);
         return intx8{int(lo[0]), int(lo[1]), int(lo[2]), int(lo[3]), int(hi[0]), int(hi[1]), int(hi[2]), int(hi[3])};
     };
-    // Scale bytes of 60 panels (a multiple of NS) from panel `at` on, one per
-    // lane.
+    // scale bytes of the wave's next 60 panels, one per lane
     int scale_a = 127, scale_b = 127;
-    auto scales = [&](int at) {
-        const int p = min(wave + (at + lane) * NW, nk - 1);
-        scale_a = sA[p];
-        scale_b = sB[p];
-    };
-    // (awaited here: with the loads pending into the K loop the compiler
-    // waits for everything at its head)
-    auto scales_here = [&]() { asm volatile("" : "+v"(scale_a), "+v"(scale_b)); };
-    // Panel i (its scales in lane `slot`) in stage S.  MORE: NS - 1 newer
-    // panels are in flight and may stay so, and panel i + NS exists.
-    auto step = [&](int i, int slot, uint8_t* S, auto more) {
-        constexpr bool MORE = decltype(more)::value;
-        constexpr int FLY = MORE ? (NS - 1) * COPIES : 0;
-        __builtin_amdgcn_s_waitcnt(0x0f70 | (FLY & 15) | (FLY >> 4 << 14));   // vmcnt(FLY)
-        const uint8_t* L = S + wave * STAGE;
-        intx8 a[2][V], b[2][H];
+    intx8 a[2][V], b[2][H];
+    stream_loop<BM, BN>(
+        S0 + wave * STAGE, S1 + wave * STAGE, n,
+        [&](uint8_t* L, int i) {
+            const uint32_t k0 = uint32_t(wave + i * NW) * 128u;
+            direct_copy<BM, 1>(qa, ld32, k0, L, 0, lane);
+            direct_copy<BN, 1>(qb, ld32, k0, L + BM * 128, 0, lane);
+        },
+        [&](const uint8_t* L) {
 #pragma unroll
-        for (int s = 0; s < 2; ++s) {
+            for (int s = 0; s < 2; ++s) {
 #pragma unroll
-            for (int v = 0; v < V; ++v) a[s][v] = frag(L, 32 * v + c, s);
+                for (int v = 0; v < V; ++v) a[s][v] = frag(L, 32 * v + c, s);
 #pragma unroll
-            for (int v = 0; v < H; ++v) b[s][v] = frag(L + BM * 128, 32 * v + c, s);
-        }
-        __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0): the stage is read
-        if constexpr (MORE) copy(S, i + NS);
-        const int sa = __builtin_amdgcn_readlane(scale_a, slot), sb = __builtin_amdgcn_readlane(scale_b, slot);
+                for (int v = 0; v < H; ++v) b[s][v] = frag(L + BM * 128, 32 * v + c, s);
+            }
+        },
+        [&](int slot) {
+            const int sa = __builtin_amdgcn_readlane(scale_a, slot), sb = __builtin_amdgcn_readlane(scale_b, slot);
 #pragma unroll
-        for (int s = 0; s < 2; ++s)
+            for (int s = 0; s < 2; ++s)
 #pragma unroll
-            for (int v = 0; v < V; ++v)
+                for (int v = 0; v < V; ++v)
 #pragma unroll
-                for (int w = 0; w < H; ++w)
-                    acc[v][w] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a[s][v], b[s][w], acc[v][w], 0, 0, 0,
-                                                                                sa, 0, sb);
-    };
-    using Yes = std::integral_constant<bool, true>;
-    using No = std::integral_constant<bool, false>;
-    // NS panels at a time, so that each one's stage is a compile-time choice,
-    // and without a branch while panels remain to be copied (with one the
-    // compiler waits for every copy in flight before each panel).
-    int i = 0, at = 0;
-    scales(0);
-    if (n > 0) copy(S0, 0);
-    if (n > 1) copy(S1, 1);
-    scales_here();
-    for (;;) {
-        const int lim = at + 60;
-        for (; i < lim && i + 2 * NS - 1 < n; i += NS) {
-            step(i, i - at, S0, Yes{});
-            step(i + 1, i + 1 - at, S1, Yes{});
-        }
-        if (i < lim) break;
-        at = i;
-        scales(at);
-        scales_here();
-    }
-    // the last panels, at most 2 NS - 1, some of them not yet copied
-    if (i - at + 2 * NS > 64) {
-        at = i;
-        scales(at);
-        scales_here();
-    }
-#pragma unroll
-    for (int t = 0; t < 2 * NS - 1; ++t) {
-        uint8_t* S = t % NS == 0 ? S0 : S1;
-        if (i + NS < n) step(i, i - at, S, Yes{});
-        else if (i < n) step(i, i - at, S, No{});
-        ++i;
-    }
+                    for (int w = 0; w < H; ++w)
+                        acc[v][w] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a[s][v], b[s][w], acc[v][w], 0, 0,
+                                                                                    0, sa, 0, sb);
+        },
+        [&](int at) {
+            const int p = min(wave + (at + lane) * NW, nk - 1);
+            scale_a = sA[p];
+            scale_b = sB[p];
+            // (awaited here: with the loads pending into the K loop the
+            // compiler waits for everything at its head)
+            asm volatile("" : "+v"(scale_a), "+v"(scale_b));
+        });
     // every wave's reads and copies are done: the stages are free
     __syncthreads();
     float* red = reinterpret_cast<float*>(S0);
@@ -768,7 +792,7 @@ const SgemmConfig kFp8Configs[] = {
 };
 const int kNumFp8Configs = sizeof(kFp8Configs) / sizeof(kFp8Configs[0]);
 
-hipError_t launch_gemm_fp8(int cfg, Fp8Args g, hipStream_t stream)
+hipError_t launch_gemm_fp8(int cfg, Fp8Args g, hipStream_t stream, int cus)
 {
     switch (cfg) {
     case 0: return launch_fp8_cfg<256, 256, 128, 128, false>(g, stream);
@@ -781,7 +805,14 @@ hipError_t launch_gemm_fp8(int cfg, Fp8Args g, hipStream_t stream)
     case 7: return launch_fp8_direct<256, 256, 128, 64, false>(g, stream);
     case 8: return launch_fp8_direct<128, 128, 64, 64, false>(g, stream);
     case 9: return launch_fp8_direct<128, 128, 64, 64, true>(g, stream);
-    case 10: return launch_fp8_direct<128, 128, 64, 32, false>(g, stream);
+    case 10: {
+        const int64_t n = ((g.M + 127) / 128) * ((g.N + 127) / 128);
+        if (!eight_bit_ring(n, g.Kp, true, cus)) return launch_fp8_direct<128, 128, 64, 32, false>(g, stream);
+        g.tiles_m = int((g.M + 127) / 128);
+        g.tiles_n = int((g.N + 127) / 128);
+        hipLaunchKernelGGL((gemm_fp8_ring_kernel<64, 32, 5>), dim3(unsigned(n)), dim3(512), 0, stream, g);
+        return hipGetLastError();
+    }
     case 11: return launch_fp8_direct<256, 256, 64, 64, false>(g, stream);
     case 12: return launch_fp8_skinny<32, 32, 8>(g, stream);
     case 13: return launch_fp8_skinny<64, 32, 4>(g, stream);

@@ -392,6 +392,164 @@ static hipError_t launch_i8_cfg(I8Args g, hipStream_t stream)
     return hipGetLastError();
 }
 
+// The direct form through a ring of NS stages (ring_loop in tile_bytes.h), for
+// launches of at most one workgroup per compute unit.  GEMM only, us, two
+// buffers -> ring: 2048^3 17.4 -> 15.2, 1300 x 1300 x 5000 33.9 -> 23.7, 1500^3
+// 13.6 -> 11.7.
+template <int BM, int BN, int WM, int WN, int NS>
+__global__ __launch_bounds__((BM / WM) * (BN / WN) * 64)
+void gemm_i8_ring_kernel(I8Args g)
+{
+    constexpr int WAVES_N = BN / WN;
+    constexpr int NW = (BM / WM) * WAVES_N;
+    constexpr int V = WM / 32, H = WN / 32;
+    MG_RING_STAGES(NS, (BM + BN) * 128);
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm0 = (wave / WAVES_N) * WM, wn0 = (wave % WAVES_N) * WN;
+    const int c = lane & 31, h = lane >> 5;
+    int tm, tn;
+    tile_of(blockIdx.x, g.tiles_m, g.tiles_n, g.group_m, g.remap, tm, tn);
+    const int64_t m0 = int64_t(tm) * BM, n0 = int64_t(tn) * BN;
+    const uint8_t* __restrict__ qa = reinterpret_cast<const uint8_t*>(g.qA) + m0 * g.ldq;
+    const uint8_t* __restrict__ qb = reinterpret_cast<const uint8_t*>(g.qB) + n0 * g.ldq;
+    const uint32_t ld32 = uint32_t(g.ldq);
+
+    intx16 acc[V][H];
+#pragma unroll
+    for (int i = 0; i < V; ++i)
+#pragma unroll
+        for (int j = 0; j < H; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0;
+    ring_loop<NS, (BM + BN) * 8 / (NW * 64)>(
+        int(g.Kp / 128),
+        [&](auto s, int kp) {
+            uint8_t* L = ring_stage(s);
+            direct_copy<BM, NW>(qa, ld32, uint32_t(kp) * 128u, L, wave, lane);
+            direct_copy<BN, NW>(qb, ld32, uint32_t(kp) * 128u, L + BM * 128, wave, lane);
+        },
+        [&](auto s, int) {
+            const uint8_t* L = ring_stage(s);
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                intx4 a[V], b[H];
+#pragma unroll
+                for (int i = 0; i < V; ++i) a[i] = __builtin_bit_cast(intx4, ring_chunk(L, wm0 + 32 * i + c, 2 * t + h));
+#pragma unroll
+                for (int j = 0; j < H; ++j)
+                    b[j] = __builtin_bit_cast(intx4, ring_chunk(L + BM * 128, wn0 + 32 * j + c, 2 * t + h));
+#pragma unroll
+                for (int i = 0; i < V; ++i)
+#pragma unroll
+                    for (int j = 0; j < H; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[i], b[j], acc[i][j], 0, 0, 0);
+            }
+        });
+    const uint32_t alpha = uint32_t(g.alpha), beta = uint32_t(g.beta);
+    store_acc_blocks<V, H>(g.C, g.ldc, g.M, g.N, m0 + wm0, n0 + wn0, h, c, beta != 0u, acc,
+                           [&](int32_t a, int32_t c0) { return int32_t(alpha * uint32_t(a) + beta * uint32_t(c0)); });
+}
+
+// Few rows or columns: waves that stream their own K panels (stream_loop in
+// tile_bytes.h; the FP8 kernel of the same form says why), their partial tiles
+// added through LDS at the end.  GEMM only, us, 64 x 64 tiles of
+// gemm_i8_kernel -> the best of these: 64 x 8192 x 8192 35.2 -> 14.6, 500 x 500
+// x 4000 18.5 -> 6.2, 400 x 900 x 2000 11.8 -> 6.5, 700 x 700 x 6000 27.4 ->
+// 11.4.
+template <int BM, int BN, int NW>
+__global__ __launch_bounds__(NW * 64) void gemm_i8_skinny_kernel(I8Args g)
+{
+    constexpr int V = BM / 32, H = BN / 32;
+    constexpr int STAGE = (BM + BN) * 128;
+    __shared__ __attribute__((aligned(1024))) uint8_t S0[NW * STAGE];
+    __shared__ __attribute__((aligned(1024))) uint8_t S1[NW * STAGE];
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int c = lane & 31, h = lane >> 5;
+    int tm, tn;
+    tile_of(blockIdx.x, g.tiles_m, g.tiles_n, g.group_m, g.remap, tm, tn);
+    const int64_t m0 = int64_t(tm) * BM, n0 = int64_t(tn) * BN;
+    const uint8_t* __restrict__ qa = reinterpret_cast<const uint8_t*>(g.qA) + m0 * g.ldq;
+    const uint8_t* __restrict__ qb = reinterpret_cast<const uint8_t*>(g.qB) + n0 * g.ldq;
+    const uint32_t ld32 = uint32_t(g.ldq);
+
+    intx16 acc[V][H];
+#pragma unroll
+    for (int i = 0; i < V; ++i)
+#pragma unroll
+        for (int j = 0; j < H; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0;
+    const int nk = int(g.Kp / 128);
+    const int n = nk > wave ? (nk - wave + NW - 1) / NW : 0;
+    intx4 a[4][V], b[4][H];
+    stream_loop<BM, BN>(
+        S0 + wave * STAGE, S1 + wave * STAGE, n,
+        [&](uint8_t* L, int i) {
+            const uint32_t k0 = uint32_t(wave + i * NW) * 128u;
+            direct_copy<BM, 1>(qa, ld32, k0, L, 0, lane);
+            direct_copy<BN, 1>(qb, ld32, k0, L + BM * 128, 0, lane);
+        },
+        [&](const uint8_t* L) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+#pragma unroll
+                for (int v = 0; v < V; ++v) a[t][v] = __builtin_bit_cast(intx4, ring_chunk(L, 32 * v + c, 2 * t + h));
+#pragma unroll
+                for (int v = 0; v < H; ++v)
+                    b[t][v] = __builtin_bit_cast(intx4, ring_chunk(L + BM * 128, 32 * v + c, 2 * t + h));
+            }
+        },
+        [&](int) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int v = 0; v < V; ++v)
+#pragma unroll
+                    for (int w = 0; w < H; ++w)
+                        acc[v][w] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[t][v], b[t][w], acc[v][w], 0, 0, 0);
+        },
+        [](int) {});
+    // every wave's reads and copies are done: the stages are free
+    __syncthreads();
+    int32_t* red = reinterpret_cast<int32_t*>(S0);
+    static_assert(NW * BM * BN * 4 <= NW * STAGE, "partial tiles fit a stage");
+#pragma unroll
+    for (int v = 0; v < V; ++v)
+#pragma unroll
+        for (int w = 0; w < H; ++w)
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                red[(wave * BM + 32 * v + 8 * (r >> 2) + 4 * h + (r & 3)) * BN + 32 * w + c] = acc[v][w][r];
+    __syncthreads();
+    const uint32_t alpha = uint32_t(g.alpha), beta = uint32_t(g.beta);
+    const int64_t col = n0 + (tid % BN);
+    constexpr int ROWS = NW * 64 / BN;
+#pragma unroll
+    for (int q = 0; q < BM / ROWS; ++q) {
+        const int row = tid / BN + ROWS * q;
+        int32_t x = red[row * BN + (tid % BN)];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) x += red[(w * BM + row) * BN + (tid % BN)];   // within int32: K <= 131071
+        if (m0 + row < g.M && col < g.N) {
+            int32_t* p = g.C + (m0 + row) * g.ldc + col;
+            *p = int32_t(alpha * uint32_t(x) + (beta != 0u ? beta * uint32_t(*p) : 0u));
+        }
+    }
+}
+
+template <int BM, int BN, int NW>
+static hipError_t launch_i8_skinny(I8Args g, hipStream_t stream)
+{
+    g.tiles_m = int((g.M + BM - 1) / BM);
+    g.tiles_n = int((g.N + BN - 1) / BN);
+    hipLaunchKernelGGL((gemm_i8_skinny_kernel<BM, BN, NW>), dim3(g.tiles_m * g.tiles_n), dim3(NW * 64), 0, stream, g);
+    return hipGetLastError();
+}
+
 const SgemmConfig kI8Configs[] = {
     // id, BM, BN, BK, WM, WN
     {0, 256, 256, 128, 128, 64},
@@ -402,10 +560,15 @@ const SgemmConfig kI8Configs[] = {
     {5, 256, 256, 128, 128, 64},   // panels copied straight into LDS
     {6, 128, 128, 128, 64, 32},    // panels copied straight into LDS, eight 64 x 32 waves
     {7, 256, 256, 128, 64, 64},    // as 5 over sixteen 64 x 64 waves
+    // waves that each take their own K panels, without barriers (eight waves,
+    // four, four)
+    {8, 32, 32, 128, 32, 32},
+    {9, 64, 32, 128, 64, 32},
+    {10, 64, 64, 128, 64, 64},
 };
 const int kNumI8Configs = sizeof(kI8Configs) / sizeof(kI8Configs[0]);
 
-hipError_t launch_gemm_i8(int cfg, I8Args g, hipStream_t stream)
+hipError_t launch_gemm_i8(int cfg, I8Args g, hipStream_t stream, int cus)
 {
     switch (cfg) {
     case 0: return launch_i8_cfg<256, 256, 128, 64, false>(g, stream);
@@ -414,8 +577,18 @@ hipError_t launch_gemm_i8(int cfg, I8Args g, hipStream_t stream)
     case 3: return launch_i8_cfg<256, 256, 128, 64, true>(g, stream);
     case 4: return launch_i8_cfg<128, 128, 64, 64, true>(g, stream);
     case 5: return launch_i8_direct<256, 256, 128, 64>(g, stream);
-    case 6: return launch_i8_direct<128, 128, 64, 32>(g, stream);
+    case 6: {
+        const int64_t n = ((g.M + 127) / 128) * ((g.N + 127) / 128);
+        if (!eight_bit_ring(n, g.Kp, false, cus)) return launch_i8_direct<128, 128, 64, 32>(g, stream);
+        g.tiles_m = int((g.M + 127) / 128);
+        g.tiles_n = int((g.N + 127) / 128);
+        hipLaunchKernelGGL((gemm_i8_ring_kernel<128, 128, 64, 32, 5>), dim3(unsigned(n)), dim3(512), 0, stream, g);
+        return hipGetLastError();
+    }
     case 7: return launch_i8_direct<256, 256, 64, 64>(g, stream);
+    case 8: return launch_i8_skinny<32, 32, 8>(g, stream);
+    case 9: return launch_i8_skinny<64, 32, 4>(g, stream);
+    case 10: return launch_i8_skinny<64, 64, 4>(g, stream);
     default: return hipErrorInvalidValue;
     }
 }

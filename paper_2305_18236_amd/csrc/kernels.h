@@ -81,7 +81,7 @@ extern const SgemmConfig kFp8Configs[];
 extern const int kNumFp8Configs;
 
 hipError_t launch_fp8_pack(const PackOperand* ops, int count, int64_t Kd, int64_t Kp, hipStream_t stream);
-hipError_t launch_gemm_fp8(int cfg, Fp8Args g, hipStream_t stream);
+hipError_t launch_gemm_fp8(int cfg, Fp8Args g, hipStream_t stream, int cus);
 
 // One problem of a batched launch, as the persistent kernel reads it.
 struct BatchProblem {
@@ -141,7 +141,18 @@ struct I8Args {
 extern const SgemmConfig kI8Configs[];
 extern const int kNumI8Configs;
 hipError_t launch_i8_pack(const PackOperand* ops, int count, int64_t Kd, int64_t Kp, hipStream_t stream);
-hipError_t launch_gemm_i8(int cfg, I8Args g, hipStream_t stream);
+hipError_t launch_gemm_i8(int cfg, I8Args g, hipStream_t stream, int cus);
+
+// Where the 128 x 128 tile of FP8 (config 10) and INT8 (6) runs through its
+// ring of stages: at most one workgroup per compute unit, which its LDS (160
+// KB) allows; more than four K panels, since filling the ring costs more than
+// it saves below (1024 x 4096 x 256, us, two buffers and ring: 8.0 and 8.6 in
+// FP8, 7.9 and 8.3 in INT8; 384^3 5.9 and 6.3, 5.7 and 5.9); and in FP8 at
+// most the 64 panels whose scale bytes a wave's lanes can hold.
+inline bool eight_bit_ring(int64_t tiles, int64_t Kp, bool fp8, int64_t cus)
+{
+    return tiles <= cus && Kp > 4 * 128 && (!fp8 || Kp <= 64 * 128);
+}
 hipError_t launch_scale_c_i32(int32_t* C, int64_t M, int64_t N, int64_t ldc, int32_t beta, hipStream_t stream);
 
 // Number of K ranges of a split-K launch described by g (1: no split).

@@ -589,40 +589,49 @@ int fp32_small_tile(int cfg, int64_t M, int64_t N, int64_t K, int splits, bool s
     return t * s <= cus || (t * s <= 2 * cus && (K + s - 1) / s >= 512) ? 15 : 12;
 }
 
-// FP8 outputs of fewer 256 x 256 tiles than half the compute units: the tile
-// with the least time by a model of each (us; GEMM only, fitted to 22 shapes
-// of 1 to 1024 rows, of which it picks the best in all, and never more than
-// 2 us off).  12, 13 and 14 hold one workgroup per compute unit, so they pay
-// their fixed time every round, and their first round waits for the operands
-// from HBM (6.4 TB/s); the 64 x 64 tile (3) and the 128 x 128 tile (10) hold
-// four and two, whose fixed times overlap.  E.g. 100 x 8192 x 8192: 12 31.0,
-// 13 23.4, 14 17.9, 3 36.0; 200 x 8192 x 1024: 19.2, 16.4, 12.9, 8.7.
-int fp8_small_config(int64_t M, int64_t N, int64_t K, int64_t cus)
+// FP8 and INT8 outputs of fewer 256 x 256 tiles than half the compute units:
+// the tile with the least time by a model of each, in us for the GEMM alone,
+// fitted to 49 shapes in each type (1 to 4096 rows, K 128 to 12000): it picks
+// the fastest tile in 92 of the 98 and is at most 0.7 us off.
+// The 32 x 32, 64 x 32 and 64 x 64 tiles whose waves stream their own panels
+// hold one workgroup per compute unit, so they pay their fixed time every
+// round, and their first round waits for the operands (15 TB/s, most of it
+// from the memory-side cache); the barriered 64 x 64 tile holds four, whose
+// fixed times overlap; the 128 x 128 tile runs through the ring of stages
+// where eight_bit_ring() allows, else two to a unit.  E.g. (in this order)
+// FP8 100 x 8192 x 8192: 28.9, 23.8, 18.1, 35.6, 26.4; 200 x 8192 x 1024:
+// 21.6, 16.0, 12.4, 8.6, 9.7; 1300 x 1300 x 5000: 49.7, 38.5, 28.4, 26.3,
+// 23.9; INT8 700 x 700 x 6000: 13.3, 11.4, 14.4, 27.3, 21.5.
+enum EightBitTile { kStream32, kStream64x32, kStream64, kBarrier64, kTile128 };
+
+EightBitTile eight_bit_small(bool fp8, int64_t M, int64_t N, int64_t K, int64_t cus)
 {
     struct Tile {
-        int cfg, bm, bn, waves;
+        EightBitTile tile;
+        int bm, bn, waves;
         double base, c0, step;   // us: a launch, a round, a K panel of a wave
     };
-    static const Tile kTiles[] = {
-        {12, 32, 32, 8, 1.0, 1.9, 0.64}, {13, 64, 32, 4, 1.3, 3.0, 0.41}, {14, 64, 64, 4, 0.3, 5.3, 0.49}};
+    static const Tile kTiles[] = {{kStream32, 32, 32, 8, 1.34, 1.45, 0.76},
+                                  {kStream64x32, 64, 32, 4, 1.38, 2.14, 0.60},
+                                  {kStream64, 64, 64, 4, 1.09, 3.57, 0.79}};
     auto per_cu = [&](int bm, int bn) { return double((tiles(M, N, bm, bn) + cus - 1) / cus); };
     const double nk = double((K + 127) / 128);
-    const double hbm = double(M + N) * double(K) / 6.4e6;
-    double best_us = 2.1 + 0.51 * nk + (per_cu(64, 64) - 1) * (1.2 + 0.02 * nk);
-    int best = 3;
-    // (two to a compute unit run as one round)
-    const double us10 = std::ceil(per_cu(128, 128) / 2) * (2.5 + nk * (per_cu(128, 128) > 1 ? 0.78 : 0.68));
-    if (us10 < best_us) {
-        best_us = us10;
-        best = 10;
-    }
-    for (const Tile& t : kTiles) {
-        const double loop = std::ceil(nk / t.waves) * t.step;
-        const double us = t.base + t.c0 + std::max(hbm, loop) + (per_cu(t.bm, t.bn) - 1) * (t.c0 + loop);
+    const double hbm = double(M + N) * double(K) / 15.04e6;
+    const int64_t n128 = tiles(M, N, 128, 128);
+    EightBitTile best = kTile128;
+    double best_us;
+    if (mg::eight_bit_ring(n128, int64_t(nk) * 128, fp8, cus)) best_us = 5.88 + nk * (0.27 + 0.31 * double(n128) / double(cus));
+    else best_us = std::ceil(per_cu(128, 128) / 2) * (5.52 + nk * (n128 > cus ? 1.00 : 0.63));   // two run as one round
+    auto offer = [&](EightBitTile t, double us) {
         if (us < best_us) {
             best_us = us;
-            best = t.cfg;
+            best = t;
         }
+    };
+    offer(kBarrier64, 2.94 + 0.49 * nk + (per_cu(64, 64) - 1) * (0.91 + 0.15 * nk));
+    for (const Tile& t : kTiles) {
+        const double loop = std::ceil(nk / t.waves) * t.step;
+        offer(t.tile, t.base + t.c0 + std::max(hbm, loop) + (per_cu(t.bm, t.bn) - 1) * (t.c0 + loop));
     }
     return best;
 }
@@ -768,7 +777,8 @@ int choose_config(int path, int64_t M, int64_t N, int64_t K, bool split_ok)
         const int64_t n256 = tiles(M, N, 256, 256);
         if (n256 > cus && n256 < 2 * cus && (n256 - cus) * 3 < cus) return 10;
         if (n256 * 2 > cus) return 11;
-        return fp8_small_config(M, N, K, cus);
+        static const int kFp8Small[] = {12, 13, 14, 3, 10};   // by EightBitTile
+        return kFp8Small[eight_bit_small(true, M, N, K, cus)];
     }
     if (path == MG_CONFIGS_I8) {
         // 256 x 256: panels copied straight into LDS (5): 2255 TOP/s at
@@ -789,8 +799,8 @@ int choose_config(int path, int64_t M, int64_t N, int64_t K, bool split_ok)
         const int64_t n256 = tiles(M, N, 256, 256);
         if (n256 > cus && n256 < 2 * cus && (n256 - cus) * 4 < cus) return 6;
         if (n256 * 2 > cus) return 7;
-        if (tiles(M, N, 128, 128) >= 128) return 6;
-        return 2;
+        static const int kI8Small[] = {8, 9, 10, 2, 6};   // by EightBitTile
+        return kI8Small[eight_bit_small(false, M, N, K, cus)];
     }
     // Tiny FP32 products: no packing (the Tiling strategy) is fastest, as the
     // paper finds for small matrices (measured: 0.84x the packed time at 16^3,
@@ -966,7 +976,7 @@ int run_i8_packed(int64_t M, int64_t N, int64_t K, int32_t alpha, const int8_t* 
     const TileOrder o = tile_order(MG_CONFIGS_I8);
     g.group_m = o.group_m;
     g.remap = o.remap;
-    return hip_status(mg::launch_gemm_i8(cfg, g, stream));
+    return hip_status(mg::launch_gemm_i8(cfg, g, stream, device_cus()));
 }
 
 int run_fp8_packed(int64_t M, int64_t N, int64_t K, float alpha, const uint8_t* qA, const uint8_t* sA,
@@ -982,7 +992,7 @@ int run_fp8_packed(int64_t M, int64_t N, int64_t K, float alpha, const uint8_t* 
     const TileOrder o = tile_order(MG_PATH_FP8_T128);
     g.group_m = o.group_m;
     g.remap = o.remap;
-    return hip_status(mg::launch_gemm_fp8(cfg, g, stream));
+    return hip_status(mg::launch_gemm_fp8(cfg, g, stream, device_cus()));
 }
 
 int run_fp8_pack(const mg::PackOperand* ops, int count, int64_t K, hipStream_t stream)

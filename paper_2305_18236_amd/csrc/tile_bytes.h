@@ -187,4 +187,56 @@ MG_DEVICE uintx4 ring_chunk(const uint8_t* lds, int row, int g)
     return *reinterpret_cast<const uintx4*>(lds + row * 128 + 16 * (g ^ direct_swz(row)));
 }
 
+// ---- K panels streamed by single waves: panels `wave`, wave + NW, ... of a
+// tile go through this wave's own two-stage ring (S0, S1: its stages of (BM +
+// BN) 128-byte rows), awaited by this wave alone, so that the K loop has no
+// barrier.  A stage is read into registers whole and at once refilled, two
+// panels ahead.  copy(stage, i): issue the copies of the wave's panel i;
+// read(stage): its fragments into registers; multiply(slot): their products,
+// slot = i modulo 60; batch(i): called at the first panel of each 60 (and with
+// copies in flight, so its loads should be few).
+template <int BM, int BN, class Copy, class Read, class Multiply, class Batch>
+MG_DEVICE void stream_loop(uint8_t* S0, uint8_t* S1, int n, Copy copy, Read read, Multiply multiply, Batch batch)
+{
+    constexpr int COPIES = (BM + BN) / 8;   // copy instructions per stage
+    static_assert(COPIES < 64, "the wait counts the copies in flight");
+    // MORE: one newer panel is in flight and may stay so, and panel i + 2 exists
+    auto step = [&](int i, int slot, uint8_t* S, auto more) {
+        constexpr int FLY = decltype(more)::value ? COPIES : 0;
+        __builtin_amdgcn_s_waitcnt(0x0f70 | (FLY & 15) | (FLY >> 4 << 14));   // vmcnt(FLY)
+        read(S);
+        __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0): the stage is read
+        if constexpr (decltype(more)::value) copy(S, i + 2);
+        multiply(slot);
+    };
+    using Yes = std::integral_constant<bool, true>;
+    using No = std::integral_constant<bool, false>;
+    // Two panels at a time, so that each one's stage is a compile-time choice,
+    // and without a branch while panels remain to be copied (with one the
+    // compiler waits for every copy in flight before each panel).
+    int i = 0, at = 0;
+    if (n <= 0) return;
+    copy(S0, 0);
+    copy(S1, min(1, n - 1));   // (a single panel again, rather than a branch)
+    batch(0);
+    for (;;) {
+        const int lim = at + 60;
+        for (; i < lim && i + 3 < n; i += 2) {
+            step(i, i - at, S0, Yes{});
+            step(i + 1, i + 1 - at, S1, Yes{});
+        }
+        if (i < lim) break;
+        at = i;
+        batch(at);
+    }
+    // the last panels, at most three, some of them not yet copied
+#pragma unroll
+    for (int t = 0; t < 3; ++t) {
+        uint8_t* S = t % 2 == 0 ? S0 : S1;
+        if (i + 2 < n) step(i, i - at, S, Yes{});
+        else if (i < n) step(i, i - at, S, No{});
+        ++i;
+    }
+}
+
 }  // namespace mg
