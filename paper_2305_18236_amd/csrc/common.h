@@ -38,6 +38,9 @@ struct GemmArgs {
     // partials in order of s and applies alpha and beta.
     float* part;
     int64_t k_chunk, ldp, part_stride;
+    // SYR2K: the panels of both products that sgemm_tile multiplies (set in
+    // the kernel), and the workgroups of a balanced split (0: none).
+    int p0, p1, share;
 };
 
 // The GEMM one workgroup of a split-K launch computes (see GemmArgs::part).

@@ -19,6 +19,16 @@
 
 namespace mg {
 
+// Tile (tm, tn) at place pid of the lower triangle, row by row.
+MG_DEVICE void tri_tile(int pid, int& tm, int& tn)
+{
+    int r = int((sqrtf(8.f * float(pid) + 1.f) - 1.f) * 0.5f);
+    while ((r + 1) * (r + 2) / 2 <= pid) ++r;   // fix rounding of the float root
+    while (r * (r + 1) / 2 > pid) --r;
+    tm = r;
+    tn = pid - r * (r + 1) / 2;
+}
+
 // Linear workgroup id -> tile (tm, tn) of the lower triangle (tm >= tn) of a
 // T x T tile grid: row tm holds tm + 1 tiles.  The XCD remap of tile_of()
 // comes first, so each XCD walks a contiguous range of the triangle.
@@ -30,11 +40,7 @@ MG_DEVICE void tri_tile_of(int pid, int T, int& tm, int& tn)
         const int per = total / XCDS;
         pid = (pid % XCDS) * per + pid / XCDS;
     }
-    int r = int((sqrtf(8.f * float(pid) + 1.f) - 1.f) * 0.5f);
-    while ((r + 1) * (r + 2) / 2 <= pid) ++r;   // fix rounding of the float root
-    while (r * (r + 1) / 2 > pid) --r;
-    tm = r;
-    tn = pid - r * (r + 1) / 2;
+    tri_tile(pid, tm, tn);
 }
 
 // Split form (gridDim.y = S > 1): the 2 * ceil(K / BK) panels of a tile's
@@ -43,13 +49,57 @@ MG_DEVICE void tri_tile_of(int pid, int T, int& tm, int& tn)
 // stride g.ldp) and syr2k_reduce_kernel sums the S partials of every
 // triangle entry in order of s.  Used when the triangle has too few tiles
 // to keep every compute unit busy through the last round of tiles.
+//
+// Balanced form (g.share > 0): the panels of all tiles, in a row, are dealt to
+// g.share workgroups, g.k_chunk to each, so that every resident workgroup has
+// the same work and no last round is half empty.  A workgroup multiplies the
+// panels of its piece tile by tile, and writes each partial tile to the slot
+// of its place among the tile's workgroups; the reduction sums a tile's slots
+// in order.  Bound by the matrix cores (N = K = 2048: 106 TFLOP/s), then by
+// each piece's first panel and partial tile, the reduction, and L2 misses:
+// neighbours work at different depths of K.  Whole calls, us, ranges of equal
+// depth -> balanced: 2048 x 2048 180 -> 163, where seven ranges were 952
+// workgroups in two rounds of 512 and a tile's partials are now 4.7 in the
+// mean; 4096 x 4096 1135 -> 1035 (2640 workgroups in six rounds).
 template <int BT, int BK, int WM, int WN, bool TR, int UPLO>
 __global__ __launch_bounds__((BT / WM) * (BT / WN) * 64)
 void syr2k_kernel(GemmArgs args)
 {
     __shared__ __attribute__((aligned(16))) float smem[sgemm_lds_floats<BT, BT, BK>()];
     GemmArgs g = args;
+    const int panels = 2 * int((g.K + BK - 1) / BK);
+    if (g.share > 0) {   // (the host keeps total below INT_MAX / 2)
+        const int S = int(g.k_chunk), total = g.tiles_m * (g.tiles_m + 1) / 2 * panels;
+        int w = blockIdx.x;
+        if (gridDim.x % 8 == 0) w = (w % 8) * int(gridDim.x / 8) + w / 8;   // neighbours on one XCD
+        int at = min(total, w * S);
+        const int end = min(total, at + S);
+        g.ldc = g.ldp;
+        g.alpha = 1.f;
+        g.beta = 0.f;
+        while (at < end) {
+            const int tile = at / panels;
+            g.p0 = at - tile * panels;
+            g.p1 = min(panels, g.p0 + end - at);
+            g.C = g.part + int64_t(w - tile * panels / S) * g.part_stride;
+            at += g.p1 - g.p0;
+            int tm, tn;
+            tri_tile(tile, tm, tn);
+            if (UPLO == 2) {
+                const int t = tm;
+                tm = tn;
+                tn = t;
+            }
+            sgemm_tile<BT, BT, BK, WM, WN, TR, !TR, true, UPLO, true>(g, tm, tn, smem);
+            __syncthreads();   // the panels in LDS are read out
+        }
+        return;
+    }
+    g.p0 = 0;
+    g.p1 = panels;
     if (gridDim.y > 1) {
+        g.p0 = int(blockIdx.y * g.k_chunk);
+        g.p1 = min(panels, int(g.p0 + g.k_chunk));
         g.C = g.part + int64_t(blockIdx.y) * g.part_stride;
         g.ldc = g.ldp;
         g.alpha = 1.f;
@@ -75,7 +125,9 @@ static hipError_t launch_syr2k_cfg(bool lower, bool tr, int splits, GemmArgs g, 
     constexpr int NT = (BT / WM) * (BT / WN) * 64;
     const int T = int((g.N + BT - 1) / BT);
     g.tiles_m = g.tiles_n = T;
-    const dim3 grid(unsigned(int64_t(T) * (T + 1) / 2), unsigned(splits > 1 ? splits : 1)), block(NT);
+    const dim3 grid(unsigned(g.share > 0 ? g.share : int64_t(T) * (T + 1) / 2),
+                    unsigned(g.share == 0 && splits > 1 ? splits : 1)),
+        block(NT);
     if (lower && !tr) hipLaunchKernelGGL((syr2k_kernel<BT, BK, WM, WN, false, 1>), grid, block, 0, stream, g);
     else if (lower && tr) hipLaunchKernelGGL((syr2k_kernel<BT, BK, WM, WN, true, 1>), grid, block, 0, stream, g);
     else if (!tr) hipLaunchKernelGGL((syr2k_kernel<BT, BK, WM, WN, false, 2>), grid, block, 0, stream, g);
@@ -103,14 +155,21 @@ hipError_t launch_syr2k(int cfg, bool lower, bool tr, int splits, GemmArgs g, hi
 // thread takes four consecutive columns, with 16-byte accesses where all four
 // lie in the triangle, element by element otherwise.
 __global__ __launch_bounds__(256) void syr2k_reduce_kernel(const float* __restrict__ part, int64_t ldp,
-                                                          int64_t stride, int S, float* C, int64_t N,
-                                                          int64_t ldc, float alpha, float beta, int lower)
+                                                          int64_t stride, int splits, float* C, int64_t N,
+                                                          int64_t ldc, float alpha, float beta, int lower,
+                                                          int bt, int panels, int share)
 {
     for (int64_t i = blockIdx.x; i < N; i += gridDim.x) {
         const int64_t j0 = lower ? 0 : i, j1 = lower ? i + 1 : N;
         for (int64_t q = (j0 & ~int64_t(3)) + 4 * int64_t(threadIdx.x); q < j1; q += 4 * int64_t(blockDim.x)) {
             const float* p = part + i * ldp + q;
             float* c = C + i * ldc + q;
+            int S = splits;
+            if (bt > 0) {   // (balanced: the workgroups that the tile's panels fell to)
+                const int ti = int(i / bt), tj = int(q / bt), a = max(ti, tj), b = min(ti, tj);
+                const int first = (a * (a + 1) / 2 + b) * panels;
+                S = (first + panels - 1) / share - first / share + 1;
+            }
             if (q >= j0 && q + 3 < j1) {
                 floatx4 acc = *reinterpret_cast<const floatx4*>(p);
                 for (int s = 1; s < S; ++s) {
@@ -140,11 +199,12 @@ __global__ __launch_bounds__(256) void syr2k_reduce_kernel(const float* __restri
     }
 }
 
-hipError_t launch_syr2k_reduce(const GemmArgs& g, int splits, bool lower, hipStream_t stream)
+hipError_t launch_syr2k_reduce(const GemmArgs& g, int splits, bool lower, int bt, int bk, hipStream_t stream)
 {
     const int64_t blocks = g.N < 8192 ? g.N : 8192;
     hipLaunchKernelGGL(syr2k_reduce_kernel, dim3(unsigned(blocks > 0 ? blocks : 1)), dim3(256), 0, stream, g.part,
-                       g.ldp, g.part_stride, splits, g.C, g.N, g.ldc, g.alpha, g.beta, int(lower));
+                       g.ldp, g.part_stride, splits, g.C, g.N, g.ldc, g.alpha, g.beta, int(lower),
+                       g.share > 0 ? bt : 0, int(2 * ((g.K + bk - 1) / bk)), int(g.k_chunk));
     return hipGetLastError();
 }
 

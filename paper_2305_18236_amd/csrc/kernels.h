@@ -125,7 +125,7 @@ hipError_t launch_scale_c(float* C, int64_t M, int64_t N, int64_t ldc, float bet
 bool syr2k_config_supported(int cfg);
 int syr2k_panel_depth(int cfg);
 hipError_t launch_syr2k(int cfg, bool lower, bool tr, int splits, GemmArgs g, hipStream_t stream);
-hipError_t launch_syr2k_reduce(const GemmArgs& g, int splits, bool lower, hipStream_t stream);
+hipError_t launch_syr2k_reduce(const GemmArgs& g, int splits, bool lower, int bt, int bk, hipStream_t stream);
 hipError_t launch_scale_tri(float* C, int64_t N, int64_t ldc, float beta, bool lower, hipStream_t stream);
 
 // INT8 GEMM on packed operands (see gemm_i8.hip).

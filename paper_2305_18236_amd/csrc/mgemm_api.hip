@@ -1180,15 +1180,18 @@ size_t batched_workspace(int64_t count)
 // units plus the reduction, which moves 8 bytes per triangle entry and split
 // (r = that traffic's time over one tile's matrix-core time, taken as
 // 0.18 * tiles / K from the measured FP32 rates: 0.53 TFLOP/s per CU, ~6 TB/s).
+//
+// splits: the partial copies of C that the workspace holds.  share: the
+// workgroups of a balanced split (0: `splits` ranges of equal depth).
 struct Syr2kPlan {
-    int cfg, splits;
+    int cfg, splits, share;
     int64_t chunk, ldp, stride;
     size_t bytes;
 };
 
 Syr2kPlan syr2k_plan(int64_t N, int64_t K)
 {
-    Syr2kPlan p{-1, 1, 0, 0, 0, 0};
+    Syr2kPlan p{-1, 1, 0, 0, 0, 0, 0};
     const int64_t cus = device_cus();
     auto tri = [&](int64_t b) { const int64_t t = (N + b - 1) / b; return t * (t + 1) / 2; };
     int cfg = g_forced[MG_PATH_FP32].load();
@@ -1225,6 +1228,25 @@ Syr2kPlan syr2k_plan(int64_t N, int64_t K)
         p.ldp = round_up(N, 4);
         p.stride = N * p.ldp;
         p.bytes = align256(size_t(p.splits) * size_t(p.stride) * sizeof(float));
+        // The eight-wave 128 x 128 tile holds two workgroups per compute unit.
+        // The triangle's panels are dealt to them evenly where the partials of
+        // a tile fit the copies planned above and A and B fit the memory-side
+        // cache (256 MB): workgroups then read different depths of K, with
+        // fewer L2 hits than ranges of equal depth.  N x K, us, ranges of equal
+        // depth and dealt, trans 'T': 2048 x 2048 182.6, 162.8; 2048 x 1215
+        // 118.3, 109.8; 4096 x 4096 1134.7, 1035.4; 7000 x 2000 1669.7, 1525.2;
+        // 4480 x 2048 644.8, 643.9 (the least gain of 21 shapes within); beyond
+        // it 6144 x 6144 (288 MB) 3472, 3452 and 8192 x 8192 (512 MB) 8175,
+        // 8464.  A forced count stays what it says.
+        const int64_t slots = 2 * cus;
+        if (cfg == 18 && g_forced_splits[MG_PATH_FP32].load() < 0 && 8.0 * double(N) * double(K) <= 268435456.0 &&
+            tiles_n * panels < INT_MAX / 2) {
+            const int64_t each = (tiles_n * panels + slots - 1) / slots;
+            if ((panels + 2 * each - 2) / each <= p.splits) {
+                p.share = int((tiles_n * panels + each - 1) / each);
+                p.chunk = each;
+            }
+        }
     } else {
         p.chunk = 0;
     }
@@ -1466,11 +1488,13 @@ int mg_syr2k(int path, char uplo, char trans, int64_t N, int64_t K, float alpha,
     if (!split) return hip_status(mg::launch_syr2k(plan.cfg, lower, tr, 1, g, s));
     g.part = static_cast<float*>(workspace);
     g.k_chunk = plan.chunk;
+    g.share = plan.share;
     g.ldp = plan.ldp;
     g.part_stride = plan.stride;
     hipError_t e = mg::launch_syr2k(plan.cfg, lower, tr, plan.splits, g, s);
     if (e != hipSuccess) return hip_status(e);
-    return hip_status(mg::launch_syr2k_reduce(g, plan.splits, lower, s));
+    return hip_status(mg::launch_syr2k_reduce(g, plan.splits, lower, table_of(MG_PATH_FP32).cfgs[plan.cfg].bm,
+                                               mg::syr2k_panel_depth(plan.cfg), s));
 }
 
 size_t mg_syr2k_workspace_size(int path, int64_t N, int64_t K)

@@ -304,10 +304,10 @@ MG_DEVICE void sgemm_tile(const GemmArgs& g, int tm, int tn, float* smem)
     // Panels [p0, p1) of the whole K loop.  A split SYR2K (gridDim.y > 1)
     // gives workgroup row s the range of k_chunk panels starting at s*k_chunk;
     // GEMM splits offset the operands instead (split_k_view) and run it all.
-    int p0 = 0, p1 = SYR2K ? 2 * nk : nk;
-    if (SYR2K && gridDim.y > 1) {
-        p0 = int(blockIdx.y * g.k_chunk);
-        p1 = min(p1, int(p0 + g.k_chunk));
+    int p0 = 0, p1 = nk;
+    if constexpr (SYR2K) {
+        p0 = g.p0;
+        p1 = g.p1;
     }
     // A group's panels are p0 + grp + i * KG, i = 0, 1, ...; panel i is staged
     // in set i & 1 (DEEP) or set 0 and multiplied from the group's LDS buffer
