@@ -198,8 +198,9 @@ int mg_gemm_plan(int path, int64_t M, int64_t N, int64_t K, size_t workspace_byt
  * must be square (ids 0, 3, 5, 18).  `workspace` (optional, device, 256-byte
  * aligned, mg_syr2k_workspace_size() bytes) holds partial tiles when each
  * tile's K loop is split over several workgroups (so that the triangle's
- * tiles fill the GPU's last round); with NULL or too few bytes the update
- * runs unsplit.  Partials are summed in a fixed order: results are
+ * tiles fill the GPU's last round), in ranges of equal depth or, where that is
+ * faster, in equal pieces of all tiles' loops; with NULL or too few bytes the
+ * update runs unsplit.  Partials are summed in a fixed order: results are
  * deterministic.  Argument codes follow BLAS xSYR2K: uplo -1, trans -2, N -3,
  * K -4, A -6, lda -7, B -8, ldb -9, C -11, ldc -12.
  */
@@ -211,7 +212,7 @@ size_t mg_syr2k_workspace_size(int path, int64_t N, int64_t K);
 /*
  * The tiles mg_syr2k runs for this problem with the current selection state
  * and a workspace of mg_syr2k_workspace_size() bytes: out2[0] = the square
- * FP32 configuration id (mg_config_info), out2[1] = the number of ranges each
+ * FP32 configuration id (mg_config_info), out2[1] = the most ranges a
  * tile's two-product K loop is cut into (1: no split); N == 0 or K == 0
  * (no tile kernel runs) gives -1 and 0.  Host-only: no device
  * call.  Errors: MG_ERR_UNSUPPORTED for a path other than MG_PATH_FP32 or a

@@ -39,8 +39,9 @@ struct GemmArgs {
     float* part;
     int64_t k_chunk, ldp, part_stride;
     // SYR2K: the panels of both products that sgemm_tile multiplies (set in
-    // the kernel), and the workgroups of a balanced split (0: none).
-    int p0, p1, share;
+    // the kernel); the workgroups that a balanced split deals k_chunk panels
+    // each (0: not balanced), and the most panels of one run of accumulators.
+    int p0, p1, share, chain;
 };
 
 // The GEMM one workgroup of a split-K launch computes (see GemmArgs::part).

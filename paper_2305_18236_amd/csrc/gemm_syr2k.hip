@@ -55,12 +55,15 @@ MG_DEVICE void tri_tile_of(int pid, int T, int& tm, int& tn)
 // the same work and no last round is half empty.  A workgroup multiplies the
 // panels of its piece tile by tile, and writes each partial tile to the slot
 // of its place among the tile's workgroups; the reduction sums a tile's slots
-// in order.  Bound by the matrix cores (N = K = 2048: 106 TFLOP/s), then by
-// each piece's first panel and partial tile, the reduction, and L2 misses:
-// neighbours work at different depths of K.  Whole calls, us, ranges of equal
-// depth -> balanced: 2048 x 2048 180 -> 163, where seven ranges were 952
-// workgroups in two rounds of 512 and a tile's partials are now 4.7 in the
-// mean; 4096 x 4096 1135 -> 1035 (2640 workgroups in six rounds).
+// in order.  A piece is cut into runs no longer than the ranges of the split
+// form, each added to the slot, so that no sum is a longer chain of panels:
+// one run per piece was faster (2048 x 2048: 163 us) but doubled the error
+// against 64 bits (4096 x 4096: 6.2e-7 -> 1.33e-6; with the runs 5.8e-7).
+// Bound by the matrix cores, then by each run's first panel and partial tile,
+// the reduction, and L2 misses: neighbours work at different depths of K.
+// Whole calls, us, trans 'T', ranges of equal depth -> balanced: 2048 x 2048
+// 180 -> 170, where seven ranges were 952 workgroups in two rounds of 512 and
+// a tile's partials are now 4.7 in the mean; 4096 x 4096 1144 -> 1095.
 template <int BT, int BK, int WM, int WN, bool TR, int UPLO>
 __global__ __launch_bounds__((BT / WM) * (BT / WN) * 64)
 void syr2k_kernel(GemmArgs args)
@@ -79,10 +82,9 @@ void syr2k_kernel(GemmArgs args)
         g.beta = 0.f;
         while (at < end) {
             const int tile = at / panels;
-            g.p0 = at - tile * panels;
-            g.p1 = min(panels, g.p0 + end - at);
+            const int q0 = at - tile * panels, q1 = min(panels, q0 + end - at);
             g.C = g.part + int64_t(w - tile * panels / S) * g.part_stride;
-            at += g.p1 - g.p0;
+            at += q1 - q0;
             int tm, tn;
             tri_tile(tile, tm, tn);
             if (UPLO == 2) {
@@ -90,8 +92,14 @@ void syr2k_kernel(GemmArgs args)
                 tm = tn;
                 tn = t;
             }
-            sgemm_tile<BT, BT, BK, WM, WN, TR, !TR, true, UPLO, true>(g, tm, tn, smem);
-            __syncthreads();   // the panels in LDS are read out
+            const int runs = (q1 - q0 + g.chain - 1) / g.chain;
+            for (int r = 0; r < runs; ++r) {
+                g.p0 = q0 + (q1 - q0) * r / runs;
+                g.p1 = q0 + (q1 - q0) * (r + 1) / runs;
+                g.beta = r > 0 ? 1.f : 0.f;
+                sgemm_tile<BT, BT, BK, WM, WN, TR, !TR, true, UPLO, true>(g, tm, tn, smem);
+                __syncthreads();   // the panels in LDS are read out
+            }
         }
         return;
     }

@@ -1185,13 +1185,13 @@ size_t batched_workspace(int64_t count)
 // workgroups of a balanced split (0: `splits` ranges of equal depth).
 struct Syr2kPlan {
     int cfg, splits, share;
-    int64_t chunk, ldp, stride;
+    int64_t chunk, chain, ldp, stride;
     size_t bytes;
 };
 
 Syr2kPlan syr2k_plan(int64_t N, int64_t K)
 {
-    Syr2kPlan p{-1, 1, 0, 0, 0, 0, 0};
+    Syr2kPlan p{-1, 1, 0, 0, 0, 0, 0, 0};
     const int64_t cus = device_cus();
     auto tri = [&](int64_t b) { const int64_t t = (N + b - 1) / b; return t * (t + 1) / 2; };
     int cfg = g_forced[MG_PATH_FP32].load();
@@ -1230,20 +1230,29 @@ Syr2kPlan syr2k_plan(int64_t N, int64_t K)
         p.bytes = align256(size_t(p.splits) * size_t(p.stride) * sizeof(float));
         // The eight-wave 128 x 128 tile holds two workgroups per compute unit.
         // The triangle's panels are dealt to them evenly where the partials of
-        // a tile fit the copies planned above and A and B fit the memory-side
-        // cache (256 MB): workgroups then read different depths of K, with
-        // fewer L2 hits than ranges of equal depth.  N x K, us, ranges of equal
-        // depth and dealt, trans 'T': 2048 x 2048 182.6, 162.8; 2048 x 1215
-        // 118.3, 109.8; 4096 x 4096 1134.7, 1035.4; 7000 x 2000 1669.7, 1525.2;
-        // 4480 x 2048 644.8, 643.9 (the least gain of 21 shapes within); beyond
-        // it 6144 x 6144 (288 MB) 3472, 3452 and 8192 x 8192 (512 MB) 8175,
-        // 8464.  A forced count stays what it says.
+        // a tile fit the copies planned above, where A and B fit the
+        // memory-side cache (256 MB: workgroups then read different depths of
+        // K, with fewer L2 hits than ranges of equal depth), and where a count
+        // of panels says that it takes less time: a run of accumulators costs
+        // its panels and 2 more, a last round of one workgroup per compute
+        // unit half a round.  Its ratio is within 6 % of the measured one for
+        // 22 shapes, and 1 % less time is asked for.  N x K, us, ranges of
+        // equal depth and dealt, trans 'T': 2048 x 2048 179.9, 170.2; 4096 x
+        // 4096 1144, 1095; 7000 x 2000 1668, 1583; 4096 x 1000 333.8, 310.6;
+        // left as they are 3000 x 1024 190.6, 194.7 and 4480 x 2048 644.7,
+        // 659.3; beyond 256 MB 6144 x 6144 3476, 3481.  A forced count stays
+        // what it says.
         const int64_t slots = 2 * cus;
         if (cfg == 18 && g_forced_splits[MG_PATH_FP32].load() < 0 && 8.0 * double(N) * double(K) <= 268435456.0 &&
             tiles_n * panels < INT_MAX / 2) {
             const int64_t each = (tiles_n * panels + slots - 1) / slots;
-            if ((panels + 2 * each - 2) / each <= p.splits) {
+            const int64_t n = tiles_n * p.splits, rest = n % slots;
+            const double rounds = double(n / slots) + (rest == 0 ? 0.0 : rest <= cus ? 0.5 : 1.0);
+            const double equal = rounds * double(p.chunk + 2);
+            const double runs = double((each + p.chunk - 1) / p.chunk) + std::min(double(tiles_n) / double(slots), 1.0);
+            if ((panels + 2 * each - 2) / each <= p.splits && equal > 1.01 * (double(each) + 2 * runs)) {
                 p.share = int((tiles_n * panels + each - 1) / each);
+                p.chain = p.chunk;
                 p.chunk = each;
             }
         }
@@ -1489,6 +1498,7 @@ int mg_syr2k(int path, char uplo, char trans, int64_t N, int64_t K, float alpha,
     g.part = static_cast<float*>(workspace);
     g.k_chunk = plan.chunk;
     g.share = plan.share;
+    g.chain = int(plan.chain);
     g.ldp = plan.ldp;
     g.part_stride = plan.stride;
     hipError_t e = mg::launch_syr2k(plan.cfg, lower, tr, plan.splits, g, s);

@@ -301,9 +301,9 @@ MG_DEVICE void sgemm_tile(const GemmArgs& g, int tm, int tn, float* smem)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-    // Panels [p0, p1) of the whole K loop.  A split SYR2K (gridDim.y > 1)
-    // gives workgroup row s the range of k_chunk panels starting at s*k_chunk;
-    // GEMM splits offset the operands instead (split_k_view) and run it all.
+    // Panels [p0, p1) of the whole K loop.  SYR2K's kernel sets the range
+    // (both products); GEMM splits offset the operands instead (split_k_view)
+    // and run it all.
     int p0 = 0, p1 = nk;
     if constexpr (SYR2K) {
         p0 = g.p0;
