@@ -59,8 +59,8 @@ const SgemmConfig kSgemmConfigs[] = {
     {14, 128, 128, 32, 64, 64},
     // as 12 and 13 with two K groups of waves in the workgroup (each group
     // every other panel, sums added through LDS): two waves per SIMD
-    {15, 64, 64, 32, 32, 32},
-    {16, 128, 64, 32, 64, 32},
+    {15, 64, 64, 32, 32, 32, 0, 0, 2},
+    {16, 128, 64, 32, 64, 32, 0, 0, 2},
     // as 5 with two register staging sets
     {17, 256, 256, 16, 128, 64},
     // 128 x 128 tiles of eight waves (64 x 32 or 32 x 64 each) with two
@@ -72,9 +72,9 @@ const SgemmConfig kSgemmConfigs[] = {
     {20, 128, 64, 32, 32, 32},
     // 32-row and 32-column tiles for skinny and small outputs, over four,
     // four and eight K groups of waves
-    {21, 32, 64, 32, 32, 32},
-    {22, 64, 32, 32, 32, 32},
-    {23, 32, 32, 32, 32, 32},
+    {21, 32, 64, 32, 32, 32, 0, 0, 4},
+    {22, 64, 32, 32, 32, 32, 0, 0, 4},
+    {23, 32, 32, 32, 32, 32, 0, 0, 8},
 };
 const int kNumSgemmConfigs = sizeof(kSgemmConfigs) / sizeof(kSgemmConfigs[0]);
 

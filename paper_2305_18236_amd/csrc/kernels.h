@@ -13,6 +13,7 @@ struct SgemmConfig {
     int id, bm, bn, bk, wm, wn;
     int direct;   // 1: operands loaded straight into registers (no LDS packing)
     int valu;     // 1: vector-ALU FMA micro-kernel instead of the matrix cores
+    int kg;       // K groups of waves (0: one)
 };
 
 extern const SgemmConfig kSgemmConfigs[];

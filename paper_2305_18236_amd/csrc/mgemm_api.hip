@@ -470,85 +470,6 @@ Fp32Plan fp32_plan(int64_t M, int64_t N, int64_t K, int pick, bool split_ok)
     return best;
 }
 
-// ---- FP32 outputs that are small (fewer than half a 64 x 64 tile per compute
-// unit) or skinny (under 256 rows or columns).  The ladder looks for the
-// largest tile that fills the compute units, which here multiplies mostly
-// padding (32 x 8192 x 8192 ran 256 x 256 tiles in eight K ranges: 258 us
-// where reading B takes 57), so these compare the tiles that fit them by a
-// time model: the 64 x 64 tile with one and two K groups (12, 15), the tiles
-// with 32 rows or columns (21, 22, 23) and the 128 x 128 tile (18), in 1 to
-// 16 K ranges.  A compute unit runs its workgroups in rounds of `occ`; a round
-// takes c0 plus the longer of its K iterations at `lat` each and its matrix
-// work at the rate `eff` of the peak; the product is bound below by reading
-// the operands (3.6 TB/s, from HBM) and the tiles' panels (6.3 TB/s, through
-// L2); a split adds a reduction.  The constants are fitted to 125 random
-// shapes with 20-40 plans each (device time): the plan it picks is within 1.1 %
-// of the best one in geometric mean, at most 10 %, and 22 % faster than the
-// ladder's (us, ladder -> model: 32 x 8192 x 8192 NT 258 -> 65, 7 x 4096 x
-// 4096 72 -> 20, 128 x 8192 x 8192 260 -> 155, 6939 x 27 x 2293 32 -> 27,
-// 28 x 218 x 514 13.1 -> 9.7).
-struct SmallTile {
-    int cfg, bm, bn, kg, occ;
-    float lat, c0, eff;   // us, us, fraction of the matrix-core rate
-};
-const SmallTile kSmallTiles[] = {
-    {12, 64, 64, 1, 4, 0.628f, 3.38f, 0.772f}, {15, 64, 64, 2, 2, 0.562f, 3.84f, 0.756f},
-    {21, 32, 64, 4, 1, 0.485f, 4.25f, 0.637f}, {22, 64, 32, 4, 1, 0.485f, 4.25f, 0.637f},
-    {23, 32, 32, 8, 1, 1.658f, 4.25f, 0.905f}, {18, 128, 128, 1, 2, 0.601f, 4.35f, 0.870f},
-};
-
-bool small_or_skinny(int64_t M, int64_t N, int64_t cus)
-{
-    return std::min(M, N) < 256 || 2 * tiles(M, N, 64, 64) <= cus;
-}
-
-float small_tile_us(const SmallTile& c, float M, float N, float K, float s, float chunk, float cus)
-{
-    const float panels = std::ceil(chunk / 32.f);
-    const float count = std::ceil(M / float(c.bm)) * std::ceil(N / float(c.bn));
-    const float per_cu = std::ceil(count * s / cus), full = std::floor(per_cu / float(c.occ));
-    const float iters = std::ceil(panels / float(c.kg)) * c.lat;
-    // a 32 x 32 x 32 product takes a compute unit 0.107 us at the peak rate
-    const float work = panels * float(c.bm * c.bn) * (0.107f / 1024.f) / c.eff;
-    const float rem = per_cu - full * float(c.occ);
-    float t = full * (c.c0 + std::max(iters, float(c.occ) * work));
-    if (rem > 0.f) t += c.c0 + std::max(iters, rem * work);
-    t = std::max({t, 4.f * (M * K + K * N + M * N) / 3.616e6f, 4.f * count * float(c.bm + c.bn) * K / 6.33e6f});
-    if (s > 1.f) t += 3.19f + 4.f * (s + 1.f) * M * N / 7.34e6f;
-    return t;
-}
-
-Fp32Plan small_plan(int64_t M, int64_t N, int64_t K, bool split_ok)
-{
-    // A call asks for the plan of its shape several times (workspace size,
-    // configuration, split): the last one of the thread is kept.  It depends
-    // on nothing but these values.
-    struct Memo {
-        int64_t M, N, K, cus;
-        bool split_ok;
-        Fp32Plan plan;
-    };
-    static thread_local Memo memo{-1, -1, -1, -1, false, {0, 1}};
-    const int64_t cus = device_cus();
-    if (memo.M == M && memo.N == N && memo.K == K && memo.cus == cus && memo.split_ok == split_ok) return memo.plan;
-    Fp32Plan best{15, 1};
-    float best_us = 1e30f;
-    const int64_t most = split_ok ? std::min<int64_t>(kMaxSplits, K / kSplitGrain) : 1;
-    for (int64_t s = 1; s <= std::max<int64_t>(most, 1); ++s) {
-        const int64_t chunk = s > 1 ? round_up((K + s - 1) / s, kSplitGrain) : K;
-        if (s > 1 && (K + chunk - 1) / chunk != s) continue;   // cut into fewer ranges: weighed there
-        for (const SmallTile& c : kSmallTiles) {
-            const float us = small_tile_us(c, float(M), float(N), float(K), float(s), float(chunk), float(cus));
-            if (us < best_us) {
-                best = Fp32Plan{c.cfg, int(s)};
-                best_us = us;
-            }
-        }
-    }
-    memo = Memo{M, N, K, cus, split_ok, best};
-    return best;
-}
-
 // The 64 x 64 FP32 tile with two register staging sets (12) replaces the
 // one-set form (3) wherever the rule picks that tile: measured (NN, beta
 // 0.5, % of the FP32 peak) 1024^3 46.2 -> 50.9, 1536^3 in four K ranges
@@ -587,6 +508,129 @@ int fp32_small_tile(int cfg, int64_t M, int64_t N, int64_t K, int splits, bool s
     const int64_t t = tiles(M, N, 64, 64);
     const int64_t s = splits > 0 ? effective_splits(K, splits) : (split_ok ? effective_splits(K, auto_splits(t, K)) : 1);
     return t * s <= cus || (t * s <= 2 * cus && (K + s - 1) / s >= 512) ? 15 : 12;
+}
+
+// ---- FP32 outputs that are small (fewer than half a 64 x 64 tile per compute
+// unit) or skinny (under 256 rows or columns).  The ladder looks for the
+// largest tile that fills the compute units, which here multiplies mostly
+// padding (32 x 8192 x 8192 ran 256 x 256 tiles in eight K ranges: 258 us
+// where reading B takes 57), so these compare the tiles that fit them by a
+// time model: the 64 x 64 tile with one and two K groups (12, 15), the tiles
+// with 32 rows or columns (21, 22, 23), the 128 x 128 tile (18) and the
+// ladder's largest (17), in 1 to 16 K ranges, as far as their accumulators sum
+// no longer chains than the ladder's plan (see fp32_chain).  A compute unit
+// runs its workgroups in rounds of `occ`; a round takes c0 plus the longer of
+// its K iterations at `lat` each and its matrix work at the rate `eff` of the
+// peak; the product takes at least the reading of the operands at 3.6 TB/s and
+// of the tiles' panels, through L2, at 6.3 TB/s (fitted rates, not limits of the
+// memory: 32 x 8192 x 8192 reads at 5.4 TB/s, and plans of one tile that these
+// bound are told apart by their reductions alone); a split adds a reduction.
+// The constants are fitted to 125 random shapes with 20-40 plans each (device
+// time; 17's to 25 plans, within 3 % of them).  Against the ladder's plans,
+// random shapes, in geometric mean: 110 skinny (to 255 rows, 1024-8192 deep)
+// 10 % faster (12 % without the bound on the chains), at most 13 % slower;
+// 30 small ones 16 %, at most 1 % slower (us, NN, ladder -> model: 32 x 8192 x
+// 8192 244 -> 50, 7 x 4096 x 4096 72 -> 20, 128 x 8192 x 8192 255 -> 143, 6939 x
+// 27 x 2293 28.0 -> 20.4, 28 x 218 x 514 13.9 -> 9.9).  The bound of 256 rows
+// is where the two meet: 256 x 8192 x 8192 takes the ladder's plan, 17 in eight
+// ranges (261 us; 18 in eight 275), and so does the model at 200 and 255 rows
+// (258 and 261; 18 in eight 272 and 275).
+struct SmallTile {
+    int cfg, bm, bn, occ;
+    float lat, c0, eff;   // us, us, fraction of the matrix-core rate
+};
+const SmallTile kSmallTiles[] = {
+    {12, 64, 64, 4, 0.628f, 3.38f, 0.772f}, {15, 64, 64, 2, 0.562f, 3.84f, 0.756f},
+    {21, 32, 64, 1, 0.485f, 4.25f, 0.637f}, {22, 64, 32, 1, 0.485f, 4.25f, 0.637f},
+    {23, 32, 32, 1, 1.658f, 4.25f, 0.905f}, {18, 128, 128, 2, 0.601f, 4.35f, 0.870f},
+    {17, 256, 256, 1, 0.600f, 9.80f, 0.921f},
+};
+
+bool small_or_skinny(int64_t M, int64_t N, int64_t cus)
+{
+    return std::min(M, N) < 256 || 2 * tiles(M, N, 64, 64) <= cus;
+}
+
+int k_groups(int cfg) { return std::max(1, mg::kSgemmConfigs[cfg].kg); }
+
+// The values of k that one accumulator of configuration `cfg` sums in a row.
+// A plan of small_plan() keeps it no longer than the ladder's: the rounding
+// error grows with it (RMS against 64 bits on uniform inputs, without this
+// bound -> with it: 200 x 4838 x 4725 7.1e-7 -> 3.5e-7, 249 x 7605 x 5879
+// 9.7e-7 -> 4.9e-7, 54 x 262 x 50 1.28e-7 -> 9.8e-8).
+int64_t fp32_chain(int cfg, int64_t K, int64_t splits)
+{
+    const int64_t chunk = splits > 1 ? round_up((K + splits - 1) / splits, kSplitGrain) : K;
+    const int64_t bk = mg::kSgemmConfigs[cfg].bk, kg = k_groups(cfg);
+    const int64_t panels = (chunk + bk - 1) / bk;
+    return (panels + kg - 1) / kg * bk;
+}
+
+// What the ladder runs, with its K ranges as a count.
+Fp32Plan fp32_ladder_plan(int64_t M, int64_t N, int64_t K, bool split_ok)
+{
+    const Fp32Plan fp = fp32_plan(M, N, K, ladder_choice(MG_PATH_FP32, M, N, K, device_cus(), split_ok), split_ok);
+    const int cfg = fp32_small_tile(fp.cfg, M, N, K, fp.splits, split_ok);
+    const mg::SgemmConfig& c = mg::kSgemmConfigs[cfg];
+    const int64_t s = !split_ok ? 1 : fp.splits > 0 ? fp.splits : auto_splits(tiles(M, N, c.bm, c.bn), K);
+    return Fp32Plan{cfg, int(effective_splits(K, s))};
+}
+
+float small_tile_us(const SmallTile& c, float M, float N, float K, float s, float chunk, float cus)
+{
+    const float panels = std::ceil(chunk / 32.f);
+    const float count = std::ceil(M / float(c.bm)) * std::ceil(N / float(c.bn));
+    const float per_cu = std::ceil(count * s / cus), full = std::floor(per_cu / float(c.occ));
+    const float iters = std::ceil(panels / float(k_groups(c.cfg))) * c.lat;
+    // a 32 x 32 x 32 product takes a compute unit 0.107 us at the peak rate
+    const float work = panels * float(c.bm * c.bn) * (0.107f / 1024.f) / c.eff;
+    const float rem = per_cu - full * float(c.occ);
+    float t = full * (c.c0 + std::max(iters, float(c.occ) * work));
+    if (rem > 0.f) t += c.c0 + std::max(iters, rem * work);
+    t = std::max({t, 4.f * (M * K + K * N + M * N) / 3.616e6f, 4.f * count * float(c.bm + c.bn) * K / 6.33e6f});
+    if (s > 1.f) t += 3.19f + 4.f * (s + 1.f) * M * N / 7.34e6f;
+    return t;
+}
+
+Fp32Plan small_plan(int64_t M, int64_t N, int64_t K, bool split_ok)
+{
+    // A call asks for the plan of its shape several times (workspace size,
+    // configuration, split): the last one of the thread is kept.  It depends
+    // on nothing but these values.
+    struct Memo {
+        int64_t M, N, K, cus;
+        bool split_ok;
+        Fp32Plan plan;
+    };
+    static thread_local Memo memo{-1, -1, -1, -1, false, {0, 1}};
+    const int64_t cus = device_cus();
+    if (memo.M == M && memo.N == N && memo.K == K && memo.cus == cus && memo.split_ok == split_ok) return memo.plan;
+    auto us = [&](const SmallTile& c, int64_t n) {
+        const int64_t chunk = n > 1 ? round_up((K + n - 1) / n, kSplitGrain) : K;
+        return small_tile_us(c, float(M), float(N), float(K), float(n), float(chunk), float(cus));
+    };
+    // The ladder's plan stays where it is one of these tiles and the model
+    // predicts less than 5 % from leaving it, and its chain of products is the
+    // longest that one accumulator may sum.
+    Fp32Plan best = fp32_ladder_plan(M, N, K, split_ok);
+    const int64_t longest = fp32_chain(best.cfg, K, best.splits);
+    float best_us = 1e30f;
+    for (const SmallTile& c : kSmallTiles)
+        if (c.cfg == best.cfg) best_us = 0.95f * us(c, best.splits);
+    const int64_t most = split_ok ? std::min<int64_t>(kMaxSplits, K / kSplitGrain) : 1;
+    for (int64_t s = 1; s <= std::max<int64_t>(most, 1); ++s) {
+        if (s > 1 && effective_splits(K, s) != s) continue;   // cut into fewer ranges: weighed there
+        for (const SmallTile& c : kSmallTiles) {
+            if (fp32_chain(c.cfg, K, s) > longest) continue;
+            const float t = us(c, s);
+            if (t < best_us) {
+                best = Fp32Plan{c.cfg, int(s)};
+                best_us = t;
+            }
+        }
+    }
+    memo = Memo{M, N, K, cus, split_ok, best};
+    return best;
 }
 
 // FP8 and INT8 outputs of fewer 256 x 256 tiles than half the compute units:
