@@ -323,16 +323,19 @@ int ladder_choice(int path, int64_t M, int64_t N, int64_t K, int64_t cus, bool s
             const int64_t n128 = tiles(M, N, t.cfgs[ladder[1]].bm, t.cfgs[ladder[1]].bn);
             // With at most one workgroup per compute unit the direct-copy tile
             // now runs through a ring of LDS stages (ring_loop in tile_bytes.h),
-            // which moves that bound down to half the compute units for short
-            // ranges and, for BF16 and FP16, to seven twelfths up to 1200
+            // which for BF16 and FP16 moves that bound down to half the
+            // compute units for short ranges and to seven twelfths up to 1200
             // deep (us, split -> 10 unsplit: BF16 1748 x 1253 x 2410 on 140
             // tiles 52.1 -> 32.5, 1031 x 2495 x 4208 on 180 74.8 -> 53.1, 2849
-            // x 959 x 5469 on 184 83.5 -> 71.1; bf16x3 2323 x 1032 x 1963 on
-            // 171 65.6 -> 49.3, 1181 x 1821 x 2437 on 150 74.2 -> 60.5, but
-            // 1445 x 1685 x 4921 on 168 level).
-            if (i == 0 && s16 > 1 && (path != MG_PATH_BF16X3 || K / s16 < 2048) &&
-                (n128 >= cus || (n128 * 2 >= cus && K / s16 <= 512) ||
-                 (path != MG_PATH_BF16X3 && n128 * 12 >= cus * 7 && K / s16 <= 1200)))
+            // x 959 x 5469 on 184 83.5 -> 71.1), where the rounding of the
+            // operands leaves nothing of the longer chain of products to be
+            // seen (RMS error, FP16 2422 x 1207 x 3623: 2.61129e-4 both).  Not
+            // bf16x3, whose error the chain adds to (2148 x 1204 x 2010, 160
+            // tiles: 65 -> 48 us, but 3.784e-6 -> 3.806e-6).
+            const bool x3 = path == MG_PATH_BF16X3;
+            if (i == 0 && s16 > 1 && (!x3 || K / s16 < 2048) &&
+                (n128 >= cus || (n128 * 4 >= cus * (x3 ? 3 : 2) && K / s16 <= 512) ||
+                 (!x3 && n128 * 12 >= cus * 7 && K / s16 <= 1200)))
                 return uses_planes(path, 10, M, N, K) ? 10 : ladder[1];
             if (i == 0 && s16 == 1 && n > cus && n < 2 * cus && (n - cus) * (path == MG_PATH_BF16X3 ? 3 : 4) < cus)
                 return uses_planes(path, 10, M, N, K) ? 10 : ladder[1];
@@ -690,11 +693,16 @@ EightBitTile eight_bit_small(bool fp8, int64_t M, int64_t N, int64_t K, int64_t 
 // on pre-packed planes) and `rate` per 128 x 128 outputs and resident
 // workgroup; a round costs c0 more; packing the planes and reducing a split
 // cost their launch and their traffic.  Constants fitted to 125 random shapes
-// per path with 25-40 plans each (device time of whole calls): the model's pick
-// is within 3 % (bf16x3 5 %) of the best plan in geometric mean, and 9 % (16 %)
-// faster than the ladder's (us: BF16 952 x 978 x 5977 52.8 -> 41, 398 x 1014 x
-// 4961 39.9 -> 34.6; bf16x3 893 x 907 x 2602 50.6 -> 42, 650 x 1056 x 1127 29.3
-// -> 21, 441 x 2667 x 472 26.1 -> 22).
+// per path with 25-40 plans each (device time of whole calls): BF16's pick is
+// within 3 % of the best plan in geometric mean and 9 % faster than the
+// ladder's (us: 952 x 978 x 5977 52.8 -> 41, 398 x 1014 x 4961 39.9 -> 34.6).
+// bf16x3's is held to K ranges no longer than the ladder's, whose chains of
+// products its error would show (RMS against 64 bits, without that bound ->
+// with it: 1078 x 1786 x 5662 3.820e-6 -> 3.790e-6; BF16 and FP16 round their
+// operands a hundred times more coarsely and show none of it): 11 % faster than
+// the ladder's on 60 random shapes (14 % without the bound), at most 6 % slower,
+// and within 2 % of the best such plan (us: 893 x 907 x 2602 51.7 -> 35.1, 650 x
+// 1056 x 1127 29.4 -> 20.7).
 struct FewTile {
     int cfg, bm, occ;
     float lat, c0, rate, latp;
@@ -753,14 +761,17 @@ Fp32Plan few_plan(int path, int64_t M, int64_t N, int64_t K, int ladder, bool sp
     Fp32Plan best{ladder, -1};
     float best_us = 1e30f;
     const int bm = table_of(path).cfgs[ladder].bm;
+    const int64_t ladder_s = split_ok ? effective_splits(K, splits_16bit(tiles(M, N, bm, bm), K, cus)) : 1;
+    auto range = [&](int64_t s) { return s > 1 ? round_up((K + s - 1) / s, kSplitGrain) : K; };
     for (const FewTile& c : m.tile)
         if (c.cfg == ladder || (c.cfg != 10 && c.bm == bm)) {
-            const int64_t s = split_ok ? effective_splits(K, splits_16bit(tiles(M, N, bm, bm), K, cus)) : 1;
-            best_us = std::min(best_us, (x3 ? 0.85f : 0.95f) * few_us(path, m, c, M, N, K, s, float(cus)));
+            best_us = std::min(best_us, (x3 ? 0.85f : 0.95f) * few_us(path, m, c, M, N, K, ladder_s, float(cus)));
         }
     const int64_t most = split_ok ? std::min<int64_t>(kMaxSplits, K / kSplitGrain) : 1;
     for (int64_t s = 1; s <= std::max<int64_t>(most, 1); ++s) {
         if (s > 1 && effective_splits(K, s) != s) continue;
+        // bf16x3: no longer chains of products than the ladder's (see above)
+        if (x3 && range(s) > range(ladder_s)) continue;
         for (const FewTile& c : m.tile) {
             const float us = few_us(path, m, c, M, N, K, s, float(cus));
             if (us < best_us) {
