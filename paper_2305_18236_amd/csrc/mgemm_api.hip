@@ -723,9 +723,11 @@ bool few_tiles(int path, int64_t M, int64_t N, int64_t K, int64_t cus)
     return is_16bit(path) && std::min(M, N) >= 384 && K >= 1 && K <= kMaxPrepackK && 2 * tiles(M, N, 128, 128) < cus;
 }
 
-float few_us(int path, const FewModel& m, const FewTile& c, int64_t M, int64_t N, int64_t K, int64_t s, float cus)
+// planes_ok: the workspace holds the pre-packed planes.
+float few_us(int path, const FewModel& m, const FewTile& c, int64_t M, int64_t N, int64_t K, int64_t s, float cus,
+             bool planes_ok)
 {
-    const bool planes = uses_planes(path, c.cfg, M, N, K);
+    const bool planes = planes_ok && uses_planes(path, c.cfg, M, N, K);
     const float chunk = s > 1 ? float(round_up((K + s - 1) / s, kSplitGrain)) : float(K);
     const float steps = std::ceil(chunk / 32.f);
     const float per_cu = std::ceil(float(tiles(M, N, c.bm, c.bm)) * float(s) / cus);
@@ -740,19 +742,23 @@ float few_us(int path, const FewModel& m, const FewTile& c, int64_t M, int64_t N
 }
 
 // ladder: the ladder's configuration.  splits -1: its automatic split.
-Fp32Plan few_plan(int path, int64_t M, int64_t N, int64_t K, int ladder, bool split_ok)
+// Where the workspace has no room for the planes, the tiles that take them
+// convert in the kernel and are slower than the model says of the planes (40
+// random shapes without workspace, us, 10 and 4: bf16x3 1470 x 1147 x 2573 100
+// and 80, BF16 1380 x 605 x 3416 109 and 74).
+Fp32Plan few_plan(int path, int64_t M, int64_t N, int64_t K, int ladder, bool split_ok, bool planes_ok)
 {
     // (the thread's last shape: see small_plan)
     struct Memo {
         int64_t M, N, K, cus;
         int path, ladder;
-        bool split_ok;
+        bool split_ok, planes_ok;
         Fp32Plan plan;
     };
-    static thread_local Memo memo{-1, -1, -1, -1, -1, -1, false, {0, 1}};
+    static thread_local Memo memo{-1, -1, -1, -1, -1, -1, false, false, {0, 1}};
     const int64_t cus = device_cus();
     if (memo.M == M && memo.N == N && memo.K == K && memo.cus == cus && memo.path == path && memo.ladder == ladder &&
-        memo.split_ok == split_ok)
+        memo.split_ok == split_ok && memo.planes_ok == planes_ok)
         return memo.plan;
     const bool x3 = path == MG_PATH_BF16X3;
     const FewModel& m = x3 ? kFewX3 : kFew16;
@@ -765,7 +771,7 @@ Fp32Plan few_plan(int path, int64_t M, int64_t N, int64_t K, int ladder, bool sp
     auto range = [&](int64_t s) { return s > 1 ? round_up((K + s - 1) / s, kSplitGrain) : K; };
     for (const FewTile& c : m.tile)
         if (c.cfg == ladder || (c.cfg != 10 && c.bm == bm)) {
-            best_us = std::min(best_us, (x3 ? 0.85f : 0.95f) * few_us(path, m, c, M, N, K, ladder_s, float(cus)));
+            best_us = std::min(best_us, (x3 ? 0.85f : 0.95f) * few_us(path, m, c, M, N, K, ladder_s, float(cus), planes_ok));
         }
     const int64_t most = split_ok ? std::min<int64_t>(kMaxSplits, K / kSplitGrain) : 1;
     for (int64_t s = 1; s <= std::max<int64_t>(most, 1); ++s) {
@@ -773,14 +779,15 @@ Fp32Plan few_plan(int path, int64_t M, int64_t N, int64_t K, int ladder, bool sp
         // bf16x3: no longer chains of products than the ladder's (see above)
         if (x3 && range(s) > range(ladder_s)) continue;
         for (const FewTile& c : m.tile) {
-            const float us = few_us(path, m, c, M, N, K, s, float(cus));
+            const float us = few_us(path, m, c, M, N, K, s, float(cus), planes_ok);
             if (us < best_us) {
-                best = Fp32Plan{c.cfg == 11 && !uses_planes(path, 11, M, N, K) ? 1 : c.cfg, int(s)};
+                const bool direct = c.cfg != 11 || (planes_ok && uses_planes(path, 11, M, N, K));
+                best = Fp32Plan{direct ? c.cfg : 1, int(s)};
                 best_us = us;
             }
         }
     }
-    memo = Memo{M, N, K, cus, path, ladder, split_ok, best};
+    memo = Memo{M, N, K, cus, path, ladder, split_ok, planes_ok, best};
     return best;
 }
 
@@ -799,7 +806,7 @@ int ladder_16bit(int path, int64_t M, int64_t N, int64_t K, bool split_ok)
     return pick == 2 && path != MG_PATH_BF16X3 ? 9 : pick;
 }
 
-int choose_config(int path, int64_t M, int64_t N, int64_t K, bool split_ok)
+int choose_config(int path, int64_t M, int64_t N, int64_t K, bool split_ok, bool planes_ok)
 {
     const int64_t cus = device_cus();
     if (path == MG_PATH_FP8_T128) {
@@ -865,14 +872,14 @@ int choose_config(int path, int64_t M, int64_t N, int64_t K, bool split_ok)
         return small_plan(M, N, K, split_ok).cfg;
     if (is_16bit(path)) {
         const int pick = ladder_16bit(path, M, N, K, split_ok);
-        return few_tiles(path, M, N, K, cus) ? few_plan(path, M, N, K, pick, split_ok).cfg : pick;
+        return few_tiles(path, M, N, K, cus) ? few_plan(path, M, N, K, pick, split_ok, planes_ok).cfg : pick;
     }
     const int pick = ladder_choice(path, M, N, K, cus, split_ok);
     const Fp32Plan fp = fp32_plan(M, N, K, pick, split_ok);
     return fp32_small_tile(fp.cfg, M, N, K, fp.splits, split_ok);
 }
 
-int pick_config(int path, int64_t M, int64_t N, int64_t K, bool split_ok = true);
+int pick_config(int path, int64_t M, int64_t N, int64_t K, bool split_ok = true, bool planes_ok = true);
 
 // ---- FP8 packed layout: q is Rp x Kp bytes, scales (Rp/128) x (Kp/128) bytes.
 // The GEMM kernels address a 256-row panel of q with 32-bit byte offsets, so
@@ -976,7 +983,7 @@ SplitPlan split_plan(int path, int cfg, int64_t M, int64_t N, int64_t K, bool sp
             s = fp.splits;
     }
     if (s < 0 && few_tiles(path, M, N, K, device_cus())) {
-        const Fp32Plan fp = few_plan(path, M, N, K, ladder_16bit(path, M, N, K, true), true);
+        const Fp32Plan fp = few_plan(path, M, N, K, ladder_16bit(path, M, N, K, true), true, true);
         if (fp.cfg == cfg) s = fp.splits;
     }
     if (s < 0) s = path == MG_PATH_FP32 ? auto_splits(tiles(M, N, c.bm, c.bn), K)
@@ -1059,7 +1066,8 @@ int run_fp8_pack(const mg::PackOperand* ops, int count, int64_t K, hipStream_t s
 // rule.  split_ok: whether a K split may be planned (false when the caller's
 // workspace cannot hold the partial products); an exact entry tuned with a
 // split does not apply then, since its tile was chosen for split K loops.
-int pick_config(int path, int64_t M, int64_t N, int64_t K, bool split_ok)
+// planes_ok: whether it can hold the pre-packed planes of the 16-bit paths.
+int pick_config(int path, int64_t M, int64_t N, int64_t K, bool split_ok, bool planes_ok)
 {
     int cfg = g_forced[path].load();
     if (cfg >= 0) return cfg;
@@ -1068,7 +1076,7 @@ int pick_config(int path, int64_t M, int64_t N, int64_t K, bool split_ok)
     if (e != nullptr && (split_ok || e->splits <= 1)) return e->cfg;
     cfg = table_lookup(path, M, N, K);
     if (config_valid(path, cfg)) return cfg;
-    return choose_config(path, M, N, K, split_ok);
+    return choose_config(path, M, N, K, split_ok, planes_ok);
 }
 
 // What mg_gemm runs on a non-FP8 path for a workspace of `avail` usable
@@ -1094,7 +1102,8 @@ GemmPlan plan_gemm(int path, int64_t M, int64_t N, int64_t K, size_t avail)
         p.planes = planes;
         return p;
     }
-    p.cfg = pick_config(path, M, N, K, false);
+    const bool planes_ok = !is_16bit(path) || avail >= align256(bf16_workspace(path, M, N, K).total);
+    p.cfg = pick_config(path, M, N, K, false, planes_ok);
     p.split = split_plan(path, p.cfg, M, N, K, false);
     const size_t planes_b = planes_of(p.cfg);
     p.planes = avail >= planes_b ? planes_b : 0;
