@@ -331,7 +331,7 @@ MG_DEVICE void sgemm_tile(const GemmArgs& g, int tm, int tn, float* smem)
     // panel i went to LDS one iteration ago), and pack panel i + 1 from
     // set_next half-way.
     // work: this wave's block is inside C (SKIP).
-    auto panel = [&](int i, int cur, auto set_cur, auto set_next, auto quick, auto work) {
+    auto panel = [&](int i, int cur, auto set_cur, auto set_next, auto quick, auto work) __attribute__((always_inline)) {
         using SetNext = decltype(set_next);
         if constexpr (decltype(quick)::value) {
             fetch(panel_of(i + AHEAD), set_cur, quick);
@@ -390,21 +390,31 @@ MG_DEVICE void sgemm_tile(const GemmArgs& g, int tm, int tn, float* smem)
         __syncthreads();
     };
     // Unrolled by two, so that the staging set of each panel is a compile-time
-    // choice.  While the panels fetched are all loaded whole the loop runs
+    // choice (see TURN).  While the panels fetched are all loaded whole the loop runs
     // without a branch, so that a pack waits for its own panel's loads only
     // and the newer panel's stay in flight: with the choice of how to load
     // inside the loop the compiler has to wait for all of them, which undid
     // half of what the second staging set is for (us, before -> after: 8192^3
     // 7849 -> 7593, 1024^3 24.9 -> 23.4, SYR2K 2048 x 2048 183 -> 180).
     int i = 0;
-    auto two = [&](auto quick, auto work) {
-        panel(i, 0, Set0{}, Set1{}, quick, work);
-        if (decltype(quick)::value || i + 1 < iters) panel(i + 1, 1, Set1{}, Set0{}, quick, work);
-        i += 2;
+    // One panel a turn where it is more than 64 matrix instructions and one
+    // staging set needs no choice: four such bodies (256 x 128 x 32 tiles of 128
+    // x 64 waves and larger ones) went past what the compiler inlines or keeps in
+    // registers, and the accumulators through scratch memory (4096^3, us, two
+    // -> one: configuration 2 1586 -> 1123, 7 1319 -> 1037).
+    constexpr int TURN = DEEP || V * H * STEPS <= 64 ? 2 : 1;   // panels of one turn of the loop
+    auto turn = [&](auto quick, auto work) {
+        if constexpr (TURN == 2) {
+            panel(i, 0, Set0{}, Set1{}, quick, work);
+            if (decltype(quick)::value || i + 1 < iters) panel(i + 1, 1, Set1{}, Set0{}, quick, work);
+        } else {
+            panel(i, i & 1, Set0{}, Set1{}, quick, work);
+        }
+        i += TURN;
     };
     auto k_loop = [&](auto work) {
         while (i < iters) {
-            // group 0's panel; the last one fetched by two(Yes) is group KG - 1's
+            // group 0's panel; the last one fetched by turn(Yes) is group KG - 1's
             auto at = [&]() { return p0 + i * KG; };
             int lim = nwhole;
             if (SYR2K) {
@@ -417,8 +427,8 @@ MG_DEVICE void sgemm_tile(const GemmArgs& g, int tm, int tn, float* smem)
                 }
                 lim = min(lim, p1);
             }
-            while (at() + (AHEAD + 2) * KG - 1 < lim) two(Yes{}, work);
-            two(No{}, work);
+            while (at() + (AHEAD + TURN) * KG - 1 < lim) turn(Yes{}, work);
+            turn(No{}, work);
         }
     };
     if (SKIP && !(m0 + wm0 < g.M && n0 + wn0 < g.N)) k_loop(No{});
