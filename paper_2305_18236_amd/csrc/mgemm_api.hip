@@ -973,16 +973,21 @@ SplitPlan split_plan(int path, int cfg, int64_t M, int64_t N, int64_t K, bool sp
         const ExactEntry* e = exact_lookup(path, M, N, K);
         if (e != nullptr && e->cfg == cfg && e->splits > 0) s = e->splits;
     }
+    // a configuration that the caller or the table names, not the rule, is cut
+    // as its tiles alone ask for, whatever small_plan() and few_plan() would do
+    // with it
+    const bool ruled = g_forced[path].load() < 0 && exact_lookup(path, M, N, K) == nullptr &&
+                       !config_valid(path, table_lookup(path, M, N, K));
     if (s < 0 && path == MG_PATH_FP32) {
         // the K ranges the rule chose with this configuration
-        const Fp32Plan fp = small_or_skinny(M, N, device_cus())
+        const Fp32Plan fp = ruled && small_or_skinny(M, N, device_cus())
                                 ? small_plan(M, N, K, true)
                                 : fp32_plan(M, N, K, ladder_choice(path, M, N, K, device_cus(), true), true);
         if (fp.cfg == cfg || (fp.cfg == 3 && (cfg == 12 || cfg == 15)) || (fp.cfg == 5 && cfg == 17) ||
             (fp.cfg == 0 && cfg == 18) || (fp.cfg == 4 && cfg == 20))
             s = fp.splits;
     }
-    if (s < 0 && few_tiles(path, M, N, K, device_cus())) {
+    if (s < 0 && ruled && few_tiles(path, M, N, K, device_cus())) {
         const Fp32Plan fp = few_plan(path, M, N, K, ladder_16bit(path, M, N, K, true), true, true);
         if (fp.cfg == cfg) s = fp.splits;
     }
