@@ -335,8 +335,10 @@ int mg_tuned_config(int path, int64_t M, int64_t N, int64_t K);
  * Uneven batched GEMM in ONE persistent kernel launch (paths FP32, BF16X3 and
  * BF16).  problems: HOST array of `count` problems, each with the semantics
  * and argument rules of mg_sgemm (quick returns included); problems must not
- * write overlapping C.  Every problem is tiled with its own tile shape (chosen
- * by the tuning table, else by its size), and one grid that fills the GPU
+ * write overlapping C.  Every problem is tiled with its own tile shape (the
+ * forced configuration's or the tuning table's, else the largest one, unless
+ * one tile of it is long beside the products that each workgroup gets of the
+ * whole batch), and one grid that fills the GPU
  * takes the tiles of all problems, largest first, each workgroup taking the
  * next tile when it finishes one.
  * workspace: device memory of at least mg_gemm_batched_workspace_size bytes,
@@ -349,7 +351,12 @@ int mg_tuned_config(int path, int64_t M, int64_t N, int64_t K);
  * MG_ERR_WORKSPACE; MG_ERR_UNSUPPORTED for MG_PATH_FP8_T128.
  */
 size_t mg_gemm_batched_workspace_size(int path, int64_t count);
-/* Configuration id mg_gemm_batched would use for one problem of this shape. */
+/* Configuration id mg_gemm_batched uses for one problem of this shape that is
+ * a batch by itself, on the current device (with none visible, on 256 compute
+ * units of one workgroup each).  Among others the choice depends on the whole
+ * batch, whatever it is the results are the same bit for bit.  An id names the
+ * order in which a tile sums its products, and, but for the FP32 id 3, its
+ * mg_config_info tile: the batched kernel runs that one as 64 x 128 tiles. */
 int mg_batched_config(int path, int64_t M, int64_t N, int64_t K);
 int mg_gemm_batched(int path, int64_t count, const mg_problem *problems,
                     void *workspace, size_t workspace_bytes, void *stream,

@@ -1230,6 +1230,9 @@ int device_cus()
     return n;
 }
 
+// Workgroups of the persistent batched kernel that the GPU holds at once.
+int64_t batched_slots(int path) { return int64_t(device_cus()) * mg::batched_blocks_per_cu(path); }
+
 // Batched workspace: a 256-byte header holding the work-list counter, then
 // the problem descriptors.  Both travel in one host-to-device copy, which also
 // resets the counter to 0 for every launch.
@@ -1823,7 +1826,8 @@ int mg_batched_config(int path, int64_t M, int64_t N, int64_t K)
 {
     if (!batched_path(path) || M < 0 || N < 0 || K < 0) return MG_ERR_UNSUPPORTED;
     if (beyond_int(M, N, K)) return MG_ERR_TOO_LARGE;
-    return batched_cfgs(path)[choose_batched_variant(path, M, N, K, 0)];
+    const double share = double(M) * double(N) * double(K) / double(batched_slots(path));
+    return batched_cfgs(path)[choose_batched_variant(path, M, N, K, share)];
 }
 
 size_t mg_gemm_batched_workspace_size(int path, int64_t count)
@@ -1860,7 +1864,7 @@ int run_batched(int path, int64_t count, const mg_problem* problems, void* works
         return MG_ERR_WORKSPACE;
 
     const mg::BatchedTile* shapes = path == MG_PATH_FP32 ? mg::kSgemmBatchedTile : mg::kBf16BatchedTile;
-    const int64_t slots = int64_t(device_cus()) * mg::batched_blocks_per_cu(path);
+    const int64_t slots = batched_slots(path);
     double share = 0;
     for (int64_t i = 0; i < count; ++i)
         share += double(problems[i].M) * double(problems[i].N) * double(problems[i].K);
@@ -1924,7 +1928,7 @@ int mg_gemm_batched(int path, int64_t count, const mg_problem* problems, void* w
 int mg_batched_slots(int path)
 {
     if (!batched_path(path)) return 0;
-    return int(std::min<int64_t>(int64_t(device_cus()) * mg::batched_blocks_per_cu(path), INT_MAX / 2));
+    return int(std::min<int64_t>(batched_slots(path), INT_MAX / 2));
 }
 
 int mg_gemm_batched_timed(int path, int64_t count, const mg_problem* problems, void* workspace,
