@@ -68,6 +68,18 @@ MIN_RANGE = 256          # shortest K range a split may leave (the library's kMi
 SPLIT_GRAIN = 128        # K ranges are whole multiples of this
 SPLITS = (1, 2, 3, 4, 6, 8)
 MAX_PAD = 1.5            # padded tile area over the problem's area
+# Configurations whose tile is computed by several groups of waves, each on its
+# own share of the K panels in panel buffers of its own: (path, id) -> groups.
+# (FP32: K groups; FP8 and INT8: single waves that stream their own panels.)
+GROUPS = {(FP32, 15): 2, (FP32, 16): 2, (FP32, 21): 4, (FP32, 22): 4, (FP32, 23): 8,
+          (FP8, 12): 8, (FP8, 13): 4, (FP8, 14): 4, (I8, 8): 8, (I8, 9): 4, (I8, 10): 4}
+# 8-bit configurations that copy or stream panels straight into LDS, in rows of
+# 128 bytes (the others pad them to 144); the direct 16-bit ones have BK 64.
+DIRECT_8BIT = {FP8: range(7, 15), I8: range(5, 11)}
+# Direct 128 x 128 tiles that run through a ring of RING_STAGES panels instead
+# of two where a launch has at most one workgroup per compute unit.
+RING = {(BF16X3, 10), (BF16, 10), (FP16, 10), (FP8, 10), (I8, 6)}
+RING_STAGES = 5
 
 
 @dataclass(frozen=True)
@@ -83,20 +95,38 @@ class Config:
     mfma: bool
 
     @property
+    def groups(self) -> int:
+        return GROUPS.get((self.path, self.id), 1)
+
+    @property
     def waves(self) -> int:
-        return (self.bm // self.wm) * (self.bn // self.wn)
+        return (self.bm // self.wm) * (self.bn // self.wn) * self.groups
+
+    @property
+    def row_bytes(self) -> int:
+        """LDS bytes of one panel row.  The 16-bit direct-copy configurations
+        (BK 64) hold 128-byte rows whatever the kind: 64 k of BF16 or FP16, or
+        32 k of bf16x3's two terms; the converting ones pad each term's row by
+        8 elements."""
+        if self.path in (BF16X3, BF16, FP16):
+            return 128 if self.bk == 64 else (self.bk + 8) * 2 * (2 if self.path == BF16X3 else 1)
+        if self.path in (FP8, I8):
+            return 128 if self.id in DIRECT_8BIT[self.path] else 144
+        return self.bk * OPERAND_BYTES[self.path]
 
     @property
     def lds_bytes(self) -> int:
-        """Two stages of a BM x BK and a BK x BN panel (Eq. 1); unpacked
-        configurations use no LDS.  The 16-bit direct-copy configurations
-        (BK 64) hold 128-byte panel rows whatever the kind: 64 k of BF16 or
-        FP16, or 32 k of bf16x3's two terms."""
-        if not self.packs:
-            return 0
-        if self.path in (BF16X3, BF16, FP16) and self.bk == 64:
-            return 2 * (self.bm + self.bn) * 128
-        return 2 * (self.bm + self.bn) * self.bk * OPERAND_BYTES[self.path]
+        """Two stages of a BM- and a BN-row panel per group (Eq. 1); unpacked
+        configurations use no LDS."""
+        return 2 * self.groups * (self.bm + self.bn) * self.row_bytes if self.packs else 0
+
+    def ring(self, items: int, K: int) -> bool:
+        """Whether a launch of `items` workgroups runs through the ring of
+        stages (which the 8-bit kinds use for more than four K panels, FP8 for
+        at most 64)."""
+        if (self.path, self.id) not in RING or items > CUS:
+            return False
+        return self.path not in DIRECT_8BIT or (K > 4 * 128 and (self.path != FP8 or K <= 64 * 128))
 
     @property
     def acc_registers(self) -> int:
@@ -164,8 +194,8 @@ def model_us(c: Config, M: int, N: int, K: int, splits: int, beta_nonzero: bool 
     rate = PEAK[c.path] * 1e12 / ISSUED[c.path] * SUSTAINED[c.path][cls]
     if not c.mfma:
         rate *= 0.6
-    occ = c.occupancy()
     items = tiles(M, N, c) * splits
+    occ = 1 if c.ring(items, K) else c.occupancy()
     slots = CUS * occ
     rounds = math.ceil(items / slots)
     fill = items / (rounds * slots)
