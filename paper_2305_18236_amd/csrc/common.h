@@ -10,7 +10,9 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef int intx8 __attribute__((ext_vector_type(8)));
 
+#ifndef MG_DEVICE   // (a CPU test compiles the panel loads as host code)
 #define MG_DEVICE __device__ __forceinline__
+#endif
 
 namespace mg {
 
