@@ -48,8 +48,11 @@ MG_DEVICE void f32_variant(const BatchProblem& p, int tm, int tn, float* smem)
     else sgemm_tile<128, 128, 32, 64, 32, TA, TB, false, 0, true, 1, true>(p.g, tm, tn, smem);
 }
 
-// Two waves per SIMD: the register budget stays at 256 per lane, so two
-// workgroups share a CU and one's epilogue overlaps the other's K loop.
+// Two workgroups share a compute unit (three of BF16's and FP16's), so that one's
+// epilogue overlaps another's K loop: FP32's of 512 threads in 128 registers a
+// lane, four waves per SIMD; bf16x3's of 256 threads in up to 256, two; BF16's
+// and FP16's in up to 168, three.
+//
 // The next work item for the whole workgroup: thread 0 takes it from the
 // counter and hands it to the others through the first 8 bytes of the panel
 // buffer.  That buffer is free here: every tile ends its K loop with a

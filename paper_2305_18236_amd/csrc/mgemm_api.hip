@@ -906,14 +906,13 @@ Fp8Workspace fp8_workspace(int64_t M, int64_t N, int64_t K)
     return w;
 }
 
-// ---- BF16 paths, pre-packed form: hi (and lo) planes of op(A) and op(B)^T,
-// rows padded to 256, K padded to 128, bf16.  Used where converting each
-// operand once beats converting it in every workgroup that reads it, as
-// measured at 8192^3 on MI355X: plain BF16 (687 vs 482 TFLOP/s: the packed
-// operands also halve the GEMM's global traffic) for min(M, N) >= 512.  On
-// bf16x3 the packed operands are as large as the FP32 ones and the in-kernel
-// conversion hides behind the matrix core (about 370 vs 347 TFLOP/s), so
-// bf16x3 converts in the kernel.
+// ---- 16-bit paths, pre-packed form: planes of op(A) and op(B)^T, rows padded
+// to 256, K padded to 128, 16 bits an element (bf16x3: its two terms
+// interleaved).  Used where converting each operand once beats converting it in
+// every workgroup that reads it, as measured at 8192^3 on MI355X: plain BF16 (687
+// vs 482 TFLOP/s: the packed operands also halve the GEMM's global traffic) for
+// min(M, N) >= 512; bf16x3, whose packed operands are as large as the FP32 ones,
+// for its direct-copy configurations only (see uses_planes).
 // The packed-operand kernels address a 256-row panel with 32-bit byte
 // offsets (row * row stride), so the pre-packed planes are used only while
 // 256 rows of up to 4 bytes per k (bf16x3's interleaved terms) stay within
